@@ -213,9 +213,11 @@ wnnc_status wnnc_get_tile(wnnc_ctx ctx, int *tpl);
 
 /* Load balance of the traversal: with visits > 0 and tile shape 1, the
  * walk of a 64-target group that takes more than `visits` node visits (as
- * recorded by wnnc_build) runs as several wavefronts over consecutive
+ * planned by wnnc_build) runs as several wavefronts over consecutive
  * node ranges, each rebuilding its lanes' decisions at the range's
  * ancestors, and a combining pass adds their FP64 sums in range order.
+ * Clouds too small to fill the chip with parts of that size are cut into
+ * shorter ones.
  * The decisions and terms are those of the whole walk (Alg. 4); only the
  * FP64 summation order changes.  0 = whole walks; default 256.  visits in
  * 0..WNNC_MAX_SPLIT.  Synchronizes when a tree exists. */

@@ -317,6 +317,16 @@ wnnc_status wnnc_destroy(wnnc_ctx ctx) {
     ctx->qslot.release();
     ctx->qcloud.release();
     ctx->cells.release();
+    ctx->groups.release();
+    ctx->plan.release();
+    ctx->plan_sum.release();
+    ctx->cuts.release();
+    ctx->ncuts.release();
+    ctx->part_off.release();
+    ctx->split_off.release();
+    ctx->split_groups.release();
+    ctx->split_slot.release();
+    ctx->finite_flag.release();
     ctx->knn_idx.release();
     ctx->knn_d2.release();
     ctx->feat.release();
@@ -414,31 +424,19 @@ wnnc_status wnnc_normalize_batched(wnnc_ctx ctx, const float *P, const int64_t *
     return normalize_impl(ctx, P, offsets, B, P_norm, center_scale);
 }
 
-// Records the walk of every 64-target group (node visits of the adjoint
-// traversal with the constant attribute 1/2: every weight is positive, so
-// it visits the nodes a smooth attribute would) for splitting long walks.
-static hipError_t plan_walks(wnnc_ctx_s *ctx) {
-    ctx->plan.clear();
-    TRY(make_tasks(ctx, 1, 0));
-    ctx->knn_ngroups = 0;  // the neighbour search builds its groups on first use
-    const int64_t len = (int64_t)ctx->ngroups * kPlanStride;
-    TRY(ctx->d_plan.ensure(len));
-    TRY(hipMemsetAsync(ctx->d_plan.p, 0, (size_t)len * sizeof(int32_t), ctx->stream));
-    MomArgs ma = mom_args(ctx, 0.0f);
-    ma.order = 0;  // the walk plan follows Alg. 4's acceptance only
-    ma.outs = ctx->rho.p;
-    TRY(launch_moments(ctx, MOM_CONST_HALF, ma));
-    TravArgs ta = trav_args(ctx, 0.0f);
-    ta.order = 0;
-    ta.srcs = ctx->rho.p;
-    ta.plan = ctx->d_plan.p;
-    TRY(record_plan(ctx, ta));
-    std::vector<int32_t> pl((size_t)len);
-    TRY(hipMemcpyAsync(pl.data(), ctx->d_plan.p, (size_t)len * sizeof(int32_t),
-                       hipMemcpyDeviceToHost, ctx->stream));
-    TRY(hipStreamSynchronize(ctx->stream));
-    ctx->plan.swap(pl);
-    return hipSuccess;
+// The tasks of tile shape tpl and split size `split` on the current tree.  The
+// walks are planned with the constant attribute 1/2 (every weight positive),
+// which visits the nodes a smooth attribute would; rho and the node records
+// are overwritten then.
+static hipError_t setup_tasks(wnnc_ctx_s *ctx, int tpl, int split) {
+    if (needs_plan(ctx, tpl, split)) {
+        MomArgs ma = mom_args(ctx, 0.0f);
+        ma.order = 0;  // the plan follows Alg. 4's acceptance only
+        ma.outs = ctx->rho.p;
+        const hipError_t e = launch_moments(ctx, MOM_CONST_HALF, ma);
+        if (e != hipSuccess) return e;
+    }
+    return make_tasks(ctx, tpl, split);
 }
 
 static wnnc_status build_impl(wnnc_ctx ctx, const float *P, const int64_t *offsets, int B,
@@ -467,10 +465,10 @@ static wnnc_status build_impl(wnnc_ctx ctx, const float *P, const int64_t *offse
     HIPCHK(hipEventCreate(&e0));
     HIPCHK(hipEventCreate(&e1));
     HIPCHK(hipEventRecord(e0, ctx->stream));
-    const int tpl = ctx->tpl, split = ctx->split;  // planning uses its own tasks
+    ctx->plan_ok = false;
+    ctx->knn_ngroups = 0;  // the neighbour search builds its groups on first use
     hipError_t e = build_tree(ctx, P);
-    if (e == hipSuccess) e = plan_walks(ctx);
-    if (e == hipSuccess) e = make_tasks(ctx, tpl, split);
+    if (e == hipSuccess) e = setup_tasks(ctx, ctx->tpl, ctx->split);
     const bool hi_too_big = e == hipSuccess && ctx->far_order > 0 && ctx->m > kMaxHiNodes;
     if (e == hipSuccess && ctx->far_order > 0 && !hi_too_big)
         e = ctx->momhi.ensure(ctx->m * kHiStride);
@@ -517,7 +515,7 @@ wnnc_status wnnc_set_tile(wnnc_ctx ctx, int tpl) {
     CHECK_CTX(ctx);
     if (tpl != 1 && tpl != 2 && tpl != 4) return fail(WNNC_EINVAL, "tile must be 1, 2 or 4");
     if (ctx->built) {
-        hipError_t e = make_tasks(ctx, tpl, ctx->split);
+        hipError_t e = setup_tasks(ctx, tpl, ctx->split);
         if (e != hipSuccess) return fail(WNNC_EDEVICE, "tasks: %s", hipGetErrorString(e));
     } else {
         ctx->tpl = tpl;
@@ -530,7 +528,7 @@ wnnc_status wnnc_set_split(wnnc_ctx ctx, int visits) {
     if (visits < 0 || visits > WNNC_MAX_SPLIT)
         return fail(WNNC_EINVAL, "split must be in 0..%d", WNNC_MAX_SPLIT);
     if (ctx->built) {
-        hipError_t e = make_tasks(ctx, ctx->tpl, visits);
+        hipError_t e = setup_tasks(ctx, ctx->tpl, visits);
         if (e != hipSuccess) return fail(WNNC_EDEVICE, "tasks: %s", hipGetErrorString(e));
     } else {
         ctx->split = visits;
@@ -636,7 +634,7 @@ wnnc_status wnnc_autotune(wnnc_ctx ctx, float w, wnnc_tile_time *times_out) {
     };
     double tk[WNNC_AUTOTUNE_CONFIGS];
     for (int k = 0; k < WNNC_AUTOTUNE_CONFIGS / 2; ++k) {
-        hipError_t e = make_tasks(ctx, cand[k][0], cand[k][1]);
+        hipError_t e = setup_tasks(ctx, cand[k][0], cand[k][1]);
         if (e != hipSuccess) return fail(WNNC_EDEVICE, "tasks: %s", hipGetErrorString(e));
         for (int pf = 0; pf < 2; ++pf) {
             double t;
@@ -666,7 +664,7 @@ wnnc_status wnnc_autotune(wnnc_ctx ctx, float w, wnnc_tile_time *times_out) {
         if (near.size() > 1) {
             for (int round = 0; round < kRetimeRounds; ++round) {
                 for (int c : near) {
-                    hipError_t e = make_tasks(ctx, cand[c / 2][0], cand[c / 2][1]);
+                    hipError_t e = setup_tasks(ctx, cand[c / 2][0], cand[c / 2][1]);
                     if (e != hipSuccess) return fail(WNNC_EDEVICE, "tasks: %s", hipGetErrorString(e));
                     double t;
                     RETURN_IF(time_setting(c % 2, 1, &t));
@@ -688,7 +686,7 @@ wnnc_status wnnc_autotune(wnnc_ctx ctx, float w, wnnc_tile_time *times_out) {
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     ctx->prefetch = best_pf;
-    hipError_t e = make_tasks(ctx, best, best_split);
+    hipError_t e = setup_tasks(ctx, best, best_split);
     if (e != hipSuccess) return fail(WNNC_EDEVICE, "tasks: %s", hipGetErrorString(e));
     // Then the walk per operator on the chosen tiles: the same iterations
     // with each operator's traversal launches timed (the events ride on the

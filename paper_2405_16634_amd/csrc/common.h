@@ -110,8 +110,14 @@ struct wnnc_ctx_s {
     DevBuf<int2> gtab;             // ngroups: part range of each group (when gtab_ok)
     bool gtab_ok = false;          // groups are the 64-point blocks: a moment pass can combine
     DevBuf<float> parts;           // nparts * 3 * 64
-    std::vector<int32_t> plan;     // host: recorded walks of the 64-target groups
-    DevBuf<int32_t> d_plan;
+    DevBuf<int4> groups;           // ngroups: first, last target; root, end node
+    DevBuf<int32_t> plan;          // kPlanStride per 64-target group (plan_ok)
+    bool plan_ok = false;          // the plan is the current tree's
+    unsigned long long plan_visits = 0;  // visits of all walks in the plan
+    DevBuf<unsigned long long> plan_sum;
+    DevBuf<int32_t> cuts;          // ngroups * kPlanStride: first nodes of the parts after the first
+    DevBuf<uint32_t> ncuts;        // ngroups: parts of a split walk (0: whole)
+    DevBuf<uint32_t> part_off, split_off;  // ngroups + 1: parts and split groups before each group
 
     // off-surface queries (wnnc_winding_at): sorted copies and their tasks
     DevBuf<unsigned long long> qkeys_a, qkeys_b;

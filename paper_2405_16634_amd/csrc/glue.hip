@@ -250,6 +250,16 @@ hipError_t launch_pred_disagree(wnnc_ctx_s *ctx, const float4 *mu, const float *
     return hipGetLastError();
 }
 
+__global__ __launch_bounds__(256) void k_zero_u64(unsigned long long *p, int64_t n) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) p[i] = 0ull;
+}
+
+hipError_t launch_zero_u64(unsigned long long *p, int64_t n, hipStream_t st) {
+    hipLaunchKernelGGL(k_zero_u64, dim3(nblk(n)), dim3(256), 0, st, p, n);
+    return hipGetLastError();
+}
+
 hipError_t launch_zero_f4(float4 *p, int64_t n, hipStream_t st) {
     hipLaunchKernelGGL(k_zero_f4, dim3(nblk(n)), dim3(256), 0, st, p, n);
     return hipGetLastError();

@@ -60,8 +60,11 @@ hipError_t build_tree(wnnc_ctx_s *ctx, const float *P);
 // Sorts M caller-order query points (M,3) by Morton key into ctx->qpts, with
 // their caller rows in ctx->qperm.
 hipError_t sort_queries(wnnc_ctx_s *ctx, const float *Q, int64_t M);
-// Wavefront tasks for tile shape tpl and split size `split` (node visits per
-// part, 0 = whole walks; used only with tpl = 1 and a recorded plan).
+// Wavefront tasks for tile shape tpl and split size `split` (the most node
+// visits per part, 0 = whole walks; used only with tpl = 1).  Where the tree
+// needs a plan for them (needs_plan), the node records must hold the
+// representatives of a constant attribute.
+bool needs_plan(const wnnc_ctx_s *ctx, int tpl, int split);
 hipError_t make_tasks(wnnc_ctx_s *ctx, int tpl, int split);
 
 // Moment pass (moments.hip): two launches, chunk pass then straddler pass.
@@ -83,9 +86,6 @@ inline hipError_t launch_traverse_all(wnnc_ctx_s *ctx, Op op, TravMode mode, boo
     return e != hipSuccess ? e : launch_combine(ctx, op, mode, a);
 }
 int trav_blocks(int64_t ntasks);
-// Records the walk of every 64-target group (ctx->plan) for split planning;
-// the tasks must be whole walks of single 64-target groups.
-hipError_t record_plan(wnnc_ctx_s *ctx, const TravArgs &a);
 
 // Glue (glue.hip).
 // Step length per cloud from the per-group partial sums; first = the
@@ -93,6 +93,7 @@ hipError_t record_plan(wnnc_ctx_s *ctx, const TravArgs &a);
 // one entry per cloud.
 hipError_t launch_alpha(wnnc_ctx_s *ctx, bool first, double *energy_row);
 hipError_t launch_sum_partials(const double *partial, int n, double *out, hipStream_t st);
+hipError_t launch_zero_u64(unsigned long long *p, int64_t n, hipStream_t st);
 hipError_t launch_zero_f4(float4 *p, int64_t n, hipStream_t st);
 hipError_t launch_gather_vec(const float *src, const uint32_t *perm, float4 *dst, int64_t n,
                              hipStream_t st);

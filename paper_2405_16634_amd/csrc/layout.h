@@ -31,11 +31,14 @@ __host__ __device__ inline int topo_leaf(int meta) { return (meta >> 4) & 1; }
 //   [0] hi(x_B).x, .y, .z, flags (int bits)
 //   [1] nu_B (3 floats; a scalar attribute in .x), skip (int bits)
 //   [2] lo(x_B).x, .y, .z, (c * width)^2 (the acceptance threshold)
-//   [3] first point, end point (int bits), 0, 0
+//   [3] of a leaf, first point, end point (int bits), 0, 0; of any other node
+//       the offsets of its second to eighth child from it, 16 bits each
+//       (kRecWideKids: an offset needs more; not set)
 // with x_B = hi + lo to about 2^-48 (hi = FP32 rounding of the FP64 x_B,
 // lo = FP32 rounding of the rest), so that target - x_B keeps full FP32
 // precision when the target is close to the node.
-// flags = depth | leaf << 4 | single-point leaf << 5.  A node of zero
+// flags = depth | leaf << 4 | single-point leaf << 5 | wide children << 6 |
+// number of children << kRecKidShift.  A node of zero
 // weight (every attribute in it zero) has threshold -1 and nu_B = 0: every
 // target takes it as an exact zero term, and none descends into it.
 // The traversal addresses records with 32-bit byte offsets: at most
@@ -64,6 +67,8 @@ constexpr int kMomHi = kMomBase + 16;
 constexpr int64_t kMaxNodes = int64_t(1) << 26;
 constexpr int kRecLeaf = 16;
 constexpr int kRecSingle = 32;
+constexpr int kRecWideKids = 64;
+constexpr int kRecKidShift = 8;
 // The moment pass's view of a node started inside a chunk, one int2 per
 // node: (first point, end point | depth << kMnodeEndBits) for a node that
 // ends inside the chunk it starts in, (first point, -1 - straddler slot)
@@ -115,17 +120,17 @@ enum TravMode {
     TR_TSUM = 3,        // A: block partial of s^2 only
     TR_RESCALE = 4,     // G: mu <- G |mu| / |G| (sorted float4)
     TR_SCALE = 5,       // A: block partials of s and s^2 (warm-start scale)
-    TR_PLAN = 6,        // no output: record the walk of each group (split planning)
     TR_POSGRAD = 7,     // P: out = p / (4 pi) + g grad F, caller order (position gradient)
     TR_ACCUM = 8,       // out = sum / (4 pi) + base, caller order (base in gradf)
 };
 
-// Split planning: the walk of every 64-target group is recorded as its node
-// visit count and the node at every kPlanStep-th visit (up to kPlanCap of
-// them), kPlanStride ints per group.
-constexpr int kPlanStep = 64;
-constexpr int kPlanCap = 63;
-constexpr int kPlanStride = kPlanCap + 1;
+// Split planning: the nodes that the walk of a 64-target group visits (as its
+// bounding box sees them, at most kPlanVisits) are listed in walk order, and
+// the plan holds their number and every kPlanStep-th of them, kPlanStride ints
+// per group.
+constexpr int kPlanStep = 16;
+constexpr int kPlanVisits = 4096;
+constexpr int kPlanStride = kPlanVisits / kPlanStep;
 
 // Per task, the ancestors of its first node (a part of a split walk):
 // their count, then the nodes from the cloud's root down (at most one per
@@ -190,7 +195,6 @@ struct TravArgs {
     const int32_t *chain;    // per task: ancestors of its first node (kChainStride ints)
     const int32_t *roots;    // first node of each cloud (nclouds + 1)
     float *parts;            // per part slot: 3 x 64 sums rounded to FP32 (component-major)
-    int32_t *plan;           // TR_PLAN output, kPlanStride ints per group
     int ntasks;              // wavefronts launched
     int nslots;              // groups: row stride of the per-group partial sums
     int tpl;                 // target groups of 64 per wavefront (1, 2, 4)

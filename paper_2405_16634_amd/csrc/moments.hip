@@ -178,7 +178,7 @@ struct CombOf {
 
 // One chunk (the workgroup's): for the MOM_COMB_* modes ta is the walk's
 // arguments, else null.
-template <int MODE, bool HI>
+template <int MODE, bool HI, int BATCH = kBatchFew>
 __device__ __forceinline__ void chunk_body(const MomArgs &a, const TravArgs *ta) {
     constexpr bool COMB = MODE >= MOM_COMB_RHO;
     constexpr int kMomVals = mom_vals<HI>();
@@ -221,7 +221,7 @@ __device__ __forceinline__ void chunk_body(const MomArgs &a, const TravArgs *ta)
             if (pr.y > pr.x) {
                 constexpr int OP = CombOf<MODE>::op, TM = CombOf<MODE>::mode;
                 double s = 0.0, gx = 0.0, gy = 0.0, gz = 0.0;
-                sum_parts<OP>(ta->parts, pr.x, pr.y, lane, s, gx, gy, gz);
+                sum_parts<OP, BATCH>(ta->parts, pr.x, pr.y, lane, s, gx, gy, gz);
                 double e = 0.0, e2 = 0.0;
                 unsigned nflip = 0;
                 if (i < a.n) finish_target<OP, TM>(*ta, i, s, gx, gy, gz, e, e2, nflip, cnu);
@@ -348,9 +348,9 @@ __global__ __launch_bounds__(kChunk) void k_moments_chunk(MomArgs a) {
 
 // The chunk pass that also runs the combining pass of the walk launched
 // before it (MOM_COMB_*; without the far field).
-template <int MODE>
+template <int MODE, int BATCH>
 __global__ __launch_bounds__(kChunk) void k_moments_comb(MomArgs a, TravArgs ta) {
-    chunk_body<MODE, false>(a, &ta);
+    chunk_body<MODE, false, BATCH>(a, &ta);
 }
 
 // Straddlers: head + totals of the chunks in between + tail.  A straddler
@@ -478,18 +478,23 @@ hipError_t launch_moments_comb(wnnc_ctx_s *ctx, MomMode mode, const MomArgs &arg
     const dim3 grid((unsigned)((a.n + kChunk - 1) / kChunk)), block(kChunk);
     const bool last = a.n_strad <= 0;
     hipError_t e = hipErrorInvalidValue;
+    // (more than two batches of kBatchFew parts per group on average)
+    const bool many = ctx->nparts > 2 * kBatchFew * ctx->nsplit;
+    auto launch = [&](void (*few_k)(MomArgs, TravArgs), void (*many_k)(MomArgs, TravArgs)) {
+        return launch_k(ctx->lev, last, many ? many_k : few_k, grid, block, ctx->stream, a, ta);
+    };
     switch (mode) {
         case MOM_COMB_RHO:
-            e = launch_k(ctx->lev, last, k_moments_comb<MOM_COMB_RHO>, grid, block, ctx->stream, a,
-                         ta);
+            e = launch(k_moments_comb<MOM_COMB_RHO, kBatchFew>,
+                       k_moments_comb<MOM_COMB_RHO, kBatchMany>);
             break;
         case MOM_COMB_R:
-            e = launch_k(ctx->lev, last, k_moments_comb<MOM_COMB_R>, grid, block, ctx->stream, a,
-                         ta);
+            e = launch(k_moments_comb<MOM_COMB_R, kBatchFew>,
+                       k_moments_comb<MOM_COMB_R, kBatchMany>);
             break;
         case MOM_COMB_RESCALE:
-            e = launch_k(ctx->lev, last, k_moments_comb<MOM_COMB_RESCALE>, grid, block,
-                         ctx->stream, a, ta);
+            e = launch(k_moments_comb<MOM_COMB_RESCALE, kBatchFew>,
+                       k_moments_comb<MOM_COMB_RESCALE, kBatchMany>);
             break;
         default:
             break;

@@ -367,7 +367,6 @@ __global__ __launch_bounds__(kTravBlock) void k_traverse(TravArgs a) {
         }
     };
     uint32_t cnt = 0;
-    int visits = 0;
     // Deferred subtrees: a subtree that at most a.defer_k lanes of the group
     // need is not walked in lockstep; its (first node, end node) goes to
     // dent and one (entry, lane) task per such lane to dtask.  flush() then
@@ -376,7 +375,7 @@ __global__ __launch_bounds__(kTravBlock) void k_traverse(TravArgs a) {
     // task's FP64 sums to its target's slot of dacc.  The decisions and
     // terms are those of the lockstep walk; only the order of the FP64
     // additions differs.
-    constexpr bool DEFER = TPL == 1 && !PF && !HI && MODE != TR_PLAN;
+    constexpr bool DEFER = TPL == 1 && !PF && !HI;
     __shared__ int2 dent[DEFER ? kDeferEntries : 1];
     __shared__ uint16_t dtask[DEFER ? kDeferTasks : 1];
     __shared__ double dacc[DEFER ? 3 : 1][DEFER ? kWave : 1];
@@ -537,12 +536,6 @@ __global__ __launch_bounds__(kTravBlock) void k_traverse(TravArgs a) {
 
     // One node visit for all groups; returns the next node in pre-order.
     auto visit = [&](const v16f &R, int node) -> int {
-        if (MODE == TR_PLAN) {
-            if (visits > 0 && visits % kPlanStep == 0 && visits / kPlanStep <= kPlanCap &&
-                lane == 0)
-                a.plan[(int64_t)tslot * kPlanStride + visits / kPlanStep] = node;
-            ++visits;
-        }
         const int flags = __float_as_int(R[3]);
         const int skip = __float_as_int(R[7]);
         const int depth = flags & 15;
@@ -729,10 +722,6 @@ __global__ __launch_bounds__(kTravBlock) void k_traverse(TravArgs a) {
     if (COUNT) {  // cnt is wave-uniform: the pairs of all lanes
         if (lane == 0) atomicAdd(a.pairs + OP, (unsigned long long)cnt);
     }
-    if (MODE == TR_PLAN) {
-        if (lane == 0) a.plan[(int64_t)tslot * kPlanStride] = visits;
-        return;
-    }
     if (tslot < 0) {  // one part of a split walk (TPL = 1): its sums, rounded to FP32
         float *qp = a.parts + (int64_t)(-1 - tslot) * (3 * kWave);
         if (OP == OP_A) {
@@ -763,7 +752,7 @@ __global__ __launch_bounds__(kWave) void k_combine(TravArgs a, const int4 *__res
     const int lane = threadIdx.x;
     const int4 g = ldc_i4(groups + blockIdx.x);
     double s = 0.0, gx = 0.0, gy = 0.0, gz = 0.0;
-    sum_parts<OP>(a.parts, g.z, g.w, lane, s, gx, gy, gz);
+    sum_parts<OP, kBatchMany>(a.parts, g.z, g.w, lane, s, gx, gy, gz);
     double e = 0.0, e2 = 0.0;
     unsigned nflip = 0;
     const int t = g.x + lane;
@@ -857,15 +846,6 @@ hipError_t launch_combine(wnnc_ctx_s *ctx, Op op, TravMode mode, const TravArgs 
         if (mode == TR_ACCUM) return launch_comb<OP_T, TR_ACCUM>(ctx, a);
     }
     return hipErrorInvalidValue;
-}
-
-hipError_t record_plan(wnnc_ctx_s *ctx, const TravArgs &a) {
-    if (a.ntasks <= 0) return hipSuccess;
-    if (a.tpl != 1 || ctx->nsplit != 0) return hipErrorInvalidValue;
-    const dim3 grid((unsigned)trav_blocks(a.ntasks)), block(kTravBlock);
-    hipLaunchKernelGGL((k_traverse<OP_AT, TR_PLAN, false, 1, false, false>), grid, block, 0,
-                       ctx->stream, a);
-    return hipGetLastError();
 }
 
 }  // namespace wnnc
