@@ -873,10 +873,10 @@ __global__ __launch_bounds__(kPlanBlock) void k_plan(const int4 *__restrict__ gr
 // The cuts of every group's walk into parts of at most about `split` visits
 // (the first nodes of the parts after the first: nodes the plan reaches near
 // equal numbers of visits, in walk order), and the number of its parts (0: a
-// whole walk).
+// whole walk).  With step > 1, only every step-th node of the plan is a cut.
 __global__ __launch_bounds__(256) void k_cuts(const int4 *__restrict__ groups,
                                               const int32_t *__restrict__ plan, int ngroups,
-                                              int split, int32_t *__restrict__ cuts,
+                                              int split, int step, int32_t *__restrict__ cuts,
                                               uint32_t *__restrict__ nparts) {
     const int g = blockIdx.x * blockDim.x + threadIdx.x;
     if (g >= ngroups) return;
@@ -886,12 +886,13 @@ __global__ __launch_bounds__(256) void k_cuts(const int4 *__restrict__ groups,
         const int32_t *pl = plan + (int64_t)g * kPlanStride;
         int32_t *out = cuts + (int64_t)g * kPlanStride;
         const int V = pl[0];
-        const int kmax = (V - 1) / kPlanStep;
+        const int visits = kPlanStep * step;  // between two nodes that can be cuts
+        const int kmax = min((V - 1) / visits, kPlanStride / step - 1);
         const int P = min((V + split - 1) / split, kmax + 1);
         int prev = G.z;
         for (int q = 1; q < P; ++q) {
             const int v = (int)((int64_t)V * q / P);
-            const int nd = pl[min(max((v + kPlanStep / 2) / kPlanStep, 1), kmax)];
+            const int nd = pl[step * min(max((v + visits / 2) / visits, 1), kmax)];
             if (nd > prev && nd < G.w) {
                 out[cnt++] = nd;
                 prev = nd;
@@ -987,11 +988,15 @@ __global__ __launch_bounds__(256) void k_emit_tasks(
 // walk takes; below two parts per wavefront slot, more of them only add the
 // visits of their ancestors.  A walk with parts of 256 visits -> of this rule:
 // 44.1 -> 9.7 us at 2k points, 52.6 -> 20.5 us at 20k, 53.1 -> 38 us at 50k,
-// 117 -> 107 us at 200k, 338 -> 332 us at 500k (parts of 256 again, but cut
-// at every 16th visit instead of every 64th); half as many parts take 40 us at
+// 117 -> 107 us at 200k, 338 us at 500k either way; half as many parts take 40 us at
 // 50k and 84 us instead of 74 at 100k, twice as many 73 us at 50k with the
 // combining pass twice as long.
 constexpr unsigned long long kFillParts = 16384;
+// Parts of the split size itself are cut at every kCoarseStep-th node of the
+// plan (64 visits): finer cuts balance them no better than 2 % (332 instead of
+// 338 us at 500k points), and these keep the grouping, and so the bits, of the
+// sums of large clouds independent of the plan's resolution.
+constexpr int kCoarseStep = 4;
 
 // Wavefront tasks for tile shape tpl: each cloud's sorted targets cut into
 // runs of 64 * tpl, in Morton order, cloud after cloud.
@@ -1033,15 +1038,16 @@ hipError_t make_tasks(wnnc_ctx_s *ctx, int tpl, int split) {
         TRY(hipStreamSynchronize(st));
         ctx->plan_ok = true;
     }
-    int eff = 0;
+    int eff = 0, step = 1;
     if (use_plan) {
         TRY(ctx->cuts.ensure(g * kPlanStride));
         eff = (int)std::min<unsigned long long>(
             (unsigned long long)split,
             std::max<unsigned long long>(ctx->plan_visits / kFillParts, kPlanStep));
+        if (eff == split) step = kCoarseStep;
     }
     hipLaunchKernelGGL(k_cuts, dim3(blocks_for(g, 256)), dim3(256), 0, st, ctx->groups.p,
-                       ctx->plan.p, ng, eff, ctx->cuts.p, ctx->ncuts.p);
+                       ctx->plan.p, ng, eff, step, ctx->cuts.p, ctx->ncuts.p);
     hipLaunchKernelGGL(k_part_scan, dim3(1), dim3(kPartScan), 0, st, ctx->ncuts.p, ng,
                        ctx->part_off.p, ctx->split_off.p);
     uint32_t np = 0, ns = 0;
