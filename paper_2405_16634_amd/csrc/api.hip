@@ -330,12 +330,7 @@ wnnc_status wnnc_destroy(wnnc_ctx ctx) {
     ctx->knn_idx.release();
     ctx->knn_d2.release();
     ctx->feat.release();
-    ctx->mlp_h1.release();
-    ctx->mlp_h2.release();
     ctx->mlp_y.release();
-    ctx->mlp_dy.release();
-    ctx->mlp_d1.release();
-    ctx->mlp_d2.release();
     ctx->mlp_part.release();
     ctx->mlp_lpart.release();
     ctx->flip_ctr.release();

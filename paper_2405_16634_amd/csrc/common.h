@@ -141,14 +141,14 @@ struct wnnc_ctx_s {
     int last_energy_count = 0;
     DevBuf<unsigned long long> pair_ctr;  // one counter per operator kind
 
-    // warm start: neighbours, features, MLP activations and scratch
+    // warm start: neighbours, features, MLP outputs and partial gradients
     DevBuf<int4> knn_groups;       // neighbour-search groups (first, last; root, end)
     int knn_ngroups = 0;           // 0: not built for the current tree
     DevBuf<uint32_t> knn_tmp;      // 4 n: group construction
     DevBuf<int32_t> knn_idx;       // n * 16 sorted neighbour positions
     DevBuf<float> knn_d2;          // n * 16 squared distances
     DevBuf<float> feat;            // n * 48 features (caller order)
-    DevBuf<float> mlp_h1, mlp_h2, mlp_y, mlp_dy, mlp_d1, mlp_d2, mlp_part;
+    DevBuf<float> mlp_y, mlp_part;
     DevBuf<double> mlp_lpart;
     DevBuf<unsigned long long> flip_ctr;  // per cloud
     DevBuf<float> nhat;            // n * 3 predicted unit normals (caller order)

@@ -1,19 +1,37 @@
 // The neighbourhood MLP of the learned warm start: 48 -> 64 -> 64 -> 3 with
 // ReLU, BF16 operands and FP32 accumulation, inference and training.
 //
-// Every product is one generic GEMM kernel on the CDNA4 matrix cores
-// (v_mfma_f32_16x16x32_bf16): one wavefront computes a 16x16 tile of
-// C = A B over a range of K in steps of 32, with A and B read from FP32
-// memory through strides (so transposes cost nothing), rounded to BF16 (round
-// to nearest even) when the fragments are formed.  Lane l holds
-// A[l%16][8(l/16)+i] and B[8(l/16)+i][l%16], i = 0..7, and receives
-// C[4(l/16)+i][l%16], i = 0..3.  Long reductions (weight gradients, K = batch
-// size) are split over workgroups into partial tiles that a second kernel
-// adds in a fixed order, so training is reproducible bit for bit.
+// One kernel (k_mlp) runs the whole network on tiles of 32 rows, one
+// wavefront per tile, on the CDNA4 matrix cores (v_mfma_f32_16x16x32_bf16),
+// and for training also the loss, the backward pass and the tile's part of
+// the parameter gradients, which stay in accumulators until the wavefront's
+// last tile.  Lane l (r = l % 16, q = l / 16) holds A[r][8q+i] and B[8q+i][r],
+// i = 0..7, and receives C[4q+i][r], i = 0..3.  The layers are computed
+// transposed, outputs x rows (A = W^T, kept in registers; B = the rows'
+// activations), so that a lane's four outputs of one row are consecutive: they
+// go to LDS row by row, where the next layer's B fragments are 16-byte reads,
+// and, for the gradients (sums over the 32 rows: one MFMA per 16x16 tile),
+// column by column.
+//
+// What bounds it: nothing but the rows themselves has to be read (192 + 12
+// bytes each, 13 MB at 64k rows), so it is the latency of a wavefront's chain
+// of loads, LDS exchanges and 92 MFMAs per tile.  One GEMM launch per product,
+// each reading FP32 activations through strides and writing them back, with
+// one workgroup per bias gradient, took 16 launches and 590 us for a training
+// step on 64k rows, and 116 us for 100k rows of inference (1184 us for 1M);
+// this takes 32 us, and 17 us (63 us for 1M, 3.2 TB/s).
+//
+// Operands are rounded to BF16 (round to nearest even) when fragments are
+// formed; sums are FP32.  The parameter gradients are added over the tiles of
+// a wavefront, its workgroup's wavefronts and the workgroups in a fixed order,
+// so training is reproducible bit for bit.
 //
 // Parameter vector (FP32 master copy, 7491 values): W1 [48][64], b1 [64],
 // W2 [64][64], b2 [64], W3 [64][3], b3 [3]; row-major [in][out].
 #include <float.h>
+#include <string.h>
+
+#include <algorithm>
 
 #include "common.h"
 #include "internal.h"
@@ -23,124 +41,432 @@ namespace wnnc {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-// FP32 -> BF16, round to nearest even (finite inputs).
-__device__ inline __bf16 to_bf16(float f) {
-    uint32_t u = __float_as_uint(f);
-    u += 0x7fffu + ((u >> 16) & 1u);
-    return __builtin_bit_cast(__bf16, (unsigned short)(u >> 16));
-}
+// FP32 -> BF16, round to nearest even (the hardware conversion).
+__device__ inline __bf16 to_bf16(float f) { return (__bf16)f; }
 
-struct GemmArgs {
-    const float *A;
-    int64_t sam, sak;  // A(m,k) = A[m*sam + k*sak]
-    const float *B;
-    int64_t sbk, sbn;  // B(k,n) = B[k*sbk + n*sbn]
-    float *C;
-    int64_t ldc;       // C(m,n) = C[split*split_stride + m*ldc + n]
-    int64_t split_stride;
-    int M, N, K;
-    int k_per_split;   // multiple of 32
-    const float *bias; // epilogue: + bias[n]
-    int relu;          // epilogue: max(., 0)
-    const float *mask; // epilogue: zero where mask(m,n) <= 0 (same layout as C)
+constexpr int kMlpWaves = 4;    // wavefronts per workgroup
+constexpr int kMlpTile = 32;    // rows per wavefront and step
+constexpr int kMlpMaxWgs = 256; // training: workgroups (one partial gradient each)
+// LDS strides (BF16 values) of a row's 64 outputs and of a column's 32 rows;
+// multiples of 16 bytes that spread the lanes over the banks.
+constexpr int kRowStride = 72, kColStride = 40;
+
+struct MlpArgs {
+    const float *P;       // parameters
+    const float *X;       // n x 48
+    const float *L;       // labels (training), n x 3
+    float *Y;             // outputs (inference), n x 3
+    float *part;          // training: kMlpParams per workgroup
+    double *lpart;        // training: loss sum of each workgroup
+    int64_t n;
+    float inv_n;
+    int aligned;          // X is 16-byte aligned
 };
 
-__global__ __launch_bounds__(64) void k_gemm(GemmArgs g) {
-    const int l = threadIdx.x;
-    const int r = l & 15, q = l >> 4;
-    const int m0 = blockIdx.x * 16, n0 = blockIdx.y * 16;
-    const int kb = blockIdx.z * g.k_per_split;
-    const int ke = min(g.K, kb + g.k_per_split);
-    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-    const int am = m0 + r, bn = n0 + r;
-    for (int k0 = kb; k0 < ke; k0 += 32) {
-        bf16x8 a, b;
+// Eight FP32 values as a BF16 fragment.
+__device__ inline bf16x8 frag8(const float *v) {
+    bf16x8 f;
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const int k = k0 + 8 * q + i;
-            const bool kin = k < ke;
-            const float av = (kin && am < g.M) ? g.A[am * g.sam + k * g.sak] : 0.0f;
-            const float bv = (kin && bn < g.N) ? g.B[k * g.sbk + bn * g.sbn] : 0.0f;
-            a[i] = to_bf16(av);
-            b[i] = to_bf16(bv);
-        }
-        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, acc, 0, 0, 0);
-    }
-    float *C = g.C + (int64_t)blockIdx.z * g.split_stride;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int m = m0 + 4 * q + i, n = n0 + r;
-        if (m >= g.M || n >= g.N) continue;
-        float v = acc[i];
-        if (g.bias) v += g.bias[n];
-        if (g.relu) v = fmaxf(v, 0.0f);
-        if (g.mask && !(g.mask[(int64_t)m * g.ldc + n] > 0.0f)) v = 0.0f;
-        C[(int64_t)m * g.ldc + n] = v;
-    }
+    for (int i = 0; i < 8; ++i) f[i] = to_bf16(v[i]);
+    return f;
 }
 
-// out[i] = sum over splits s of part[s * stride + i], in order
-__global__ __launch_bounds__(256) void k_split_sum(const float *__restrict__ part, int splits,
-                                                   int64_t stride, int64_t count,
-                                                   float *__restrict__ out) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= count) return;
-    float s = 0.0f;
-    for (int k = 0; k < splits; ++k) s += part[k * stride + i];
-    out[i] = s;
+__device__ inline bf16x8 ld_frag(const __bf16 *p) { return *(const bf16x8 *)p; }
+
+// Keeps the compiler from moving a wavefront's own LDS accesses (which execute
+// in order) across this point.
+__device__ inline void lds_order() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
 }
 
-// column sums of an (rows x cols) row-major matrix, one workgroup per column
-__global__ __launch_bounds__(256) void k_colsum(const float *__restrict__ X, int64_t rows, int cols,
-                                                float *__restrict__ out) {
-    __shared__ float sh[256];
-    const int c = blockIdx.x;
-    float s = 0.0f;
-    for (int64_t i = threadIdx.x; i < rows; i += 256) s += X[i * cols + c];
-    sh[threadIdx.x] = s;
+__device__ inline f32x4 mma(const bf16x8 &a, const bf16x8 &b, const f32x4 &c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+}
+
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+
+template <bool TRAIN>
+__global__ __launch_bounds__(kMlpWaves *kWave, TRAIN ? 1 : 2) void k_mlp(MlpArgs g) {
+    __shared__ float sp[kMlpParams];
+    // per wavefront: the activations row by row and, for training, the
+    // features, hidden activations, their gradients and the outputs' column by
+    // column; at the end the wavefront's gradient
+    constexpr int kLds = kMlpTile * kRowStride +
+                         (TRAIN ? (kMlpIn + 4 * kMlpHidden + 16) * kColStride : 0);
+    static_assert(!TRAIN || kLds * sizeof(__bf16) >= kMlpParams * sizeof(float), "gradient fits");
+    __shared__ __attribute__((aligned(16))) __bf16 work[kMlpWaves][kLds];
+    __shared__ double lsum[kMlpWaves];
+    const int tid = threadIdx.x, lane = tid & (kWave - 1);
+    const int wv = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int r = lane & 15, q = lane >> 4;
+    {  // all of a thread's loads in flight at once
+        constexpr int kPer = (kMlpParams + kMlpWaves * kWave - 1) / (kMlpWaves * kWave);
+        float v[kPer];
+#pragma unroll
+        for (int i = 0; i < kPer; ++i)
+            v[i] = g.P[min(tid + i * kMlpWaves * kWave, kMlpParams - 1)];
+#pragma unroll
+        for (int i = 0; i < kPer; ++i)
+            if (tid + i * kMlpWaves * kWave < kMlpParams) sp[tid + i * kMlpWaves * kWave] = v[i];
+    }
     __syncthreads();
-    for (int d = 128; d > 0; d >>= 1) {
-        if (threadIdx.x < d) sh[threadIdx.x] += sh[threadIdx.x + d];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) out[c] = sh[0];
-}
 
-// loss = mean_i (1 - cos(y_i, l_i)); dy = d loss / d y.  Per-block partial
-// loss sums (FP64) are reduced in order on the host side of the call.
-__global__ __launch_bounds__(256) void k_cos_loss(const float *__restrict__ Y,
-                                                  const float *__restrict__ L, int64_t n,
-                                                  float inv_n, float *__restrict__ dY,
-                                                  double *__restrict__ part) {
-    __shared__ double sh[256];
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    // weight fragments: forward A[out][in], backward A[in][out]
+    bf16x8 w1[4][2], w2[4][2], w3[2], v3[4], v2[4][2];
+    float b1[4][4], b2[4][4], b3[3];
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            float a1[8], a2[8], c2[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const int in = 32 * k + 8 * q + i, out = 16 * m + r;
+                a1[i] = in < kMlpIn ? sp[kOffW1 + in * kMlpHidden + out] : 0.f;
+                a2[i] = sp[kOffW2 + in * kMlpHidden + out];
+                c2[i] = TRAIN ? sp[kOffW2 + out * kMlpHidden + in] : 0.f;
+            }
+            w1[m][k] = frag8(a1);
+            w2[m][k] = frag8(a2);
+            if (TRAIN) v2[m][k] = frag8(c2);
+        }
+        float c3[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+            c3[i] = TRAIN && q == 0 && i < kMlpOut ? sp[kOffW3 + (16 * m + r) * kMlpOut + i] : 0.f;
+        if (TRAIN) v3[m] = frag8(c3);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            b1[m][i] = sp[kOffB1 + 16 * m + 4 * q + i];
+            b2[m][i] = sp[kOffB2 + 16 * m + 4 * q + i];
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        float a3[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+            a3[i] = r < kMlpOut ? sp[kOffW3 + (32 * k + 8 * q + i) * kMlpOut + r] : 0.f;
+        w3[k] = frag8(a3);
+    }
+#pragma unroll
+    for (int i = 0; i < kMlpOut; ++i) b3[i] = sp[kOffB3 + i];
+
+    constexpr int kCols = kMlpHidden * kColStride;
+    __bf16 *rm = work[wv], *h1t = rm + kMlpTile * kRowStride, *h2t = h1t + kCols,
+           *d1t = h2t + kCols, *d2t = d1t + kCols, *xt = d2t + kCols,
+           *yt = xt + kMlpIn * kColStride;  // (all but rm in training only)
+    const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+    f32x4 gw1[3][4], gw2[4][4], gw3[4];
+    float gb1[4][4], gb2[4][4], gb3[3] = {0.f, 0.f, 0.f};
     double loss = 0.0;
-    if (i < n) {
-        const float y0 = Y[3 * i], y1 = Y[3 * i + 1], y2 = Y[3 * i + 2];
-        const float l0 = L[3 * i], l1 = L[3 * i + 1], l2 = L[3 * i + 2];
-        const float yy = sqrtf(y0 * y0 + y1 * y1 + y2 * y2);
-        const float ll = sqrtf(l0 * l0 + l1 * l1 + l2 * l2);
-        float d0 = 0.f, d1 = 0.f, d2 = 0.f;
-        float cs = 0.f;
-        if (yy > 0.f && ll > 0.f) {
-            const float yl = y0 * l0 + y1 * l1 + y2 * l2;
-            cs = yl / (yy * ll);
-            // d cos / d y = l/(|y||l|) - (y.l) y / (|y|^3 |l|)
-            const float a = 1.0f / (yy * ll), b = yl / (yy * yy * yy * ll);
-            d0 = -inv_n * (l0 * a - y0 * b);
-            d1 = -inv_n * (l1 * a - y1 * b);
-            d2 = -inv_n * (l2 * a - y2 * b);
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+        gw3[m] = zero;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            if (m < 3) gw1[m][k] = zero;
+            gw2[m][k] = zero;
+            gb1[m][k] = gb2[m][k] = 0.f;
         }
-        loss = 1.0 - (double)cs;
-        dY[3 * i] = d0, dY[3 * i + 1] = d1, dY[3 * i + 2] = d2;
     }
-    sh[threadIdx.x] = loss;
-    __syncthreads();
-    for (int d = 128; d > 0; d >>= 1) {
-        if (threadIdx.x < d) sh[threadIdx.x] += sh[threadIdx.x + d];
+    if (TRAIN) {  // the outputs beyond the third stay zero
+        for (int i = lane; i < 16 * kColStride; i += kWave) yt[i] = to_bf16(0.f);
+    }
+
+    // a 64 x 32 layer output (outputs x rows): to LDS row by row
+    auto put_rows = [&](const f32x4 (&h)[4][2]) {
+#pragma unroll
+        for (int m = 0; m < 4; ++m) {
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                bf16x4 o;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) o[i] = to_bf16(h[m][t][i]);
+                *(bf16x4 *)(rm + (16 * t + r) * kRowStride + 16 * m + 4 * q) = o;
+            }
+        }
+    };
+    // and column by column
+    auto put_cols = [&](__bf16 *c, const f32x4 (&h)[4][2]) {
+#pragma unroll
+        for (int m = 0; m < 4; ++m) {
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    c[(16 * m + 4 * q + i) * kColStride + 16 * t + r] = to_bf16(h[m][t][i]);
+            }
+        }
+    };
+
+    const int64_t tiles = (g.n + kMlpTile - 1) / kMlpTile;
+    for (int64_t tile = (int64_t)blockIdx.x * kMlpWaves + wv; tile < tiles;
+         tile += (int64_t)gridDim.x * kMlpWaves) {
+        const int64_t row0 = tile * kMlpTile;
+        // layer 1: the rows' features, 8 consecutive ones per lane
+        f32x4 h1[4][2], h2[4][2];
+#pragma unroll
+        for (int m = 0; m < 4; ++m) h1[m][0] = h1[m][1] = h2[m][0] = h2[m][1] = zero;
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            const int64_t row = row0 + 16 * t + r;
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                const int f0 = 32 * k + 8 * q;
+                float v[8];
+#pragma unroll
+                for (int i = 0; i < 8; ++i) v[i] = 0.f;
+                if (row < g.n && f0 < kMlpIn) {
+                    const float *xp = g.X + row * kMlpIn + f0;
+                    if (g.aligned) {
+                        const float4 u0 = *(const float4 *)xp, u1 = *(const float4 *)(xp + 4);
+                        v[0] = u0.x, v[1] = u0.y, v[2] = u0.z, v[3] = u0.w;
+                        v[4] = u1.x, v[5] = u1.y, v[6] = u1.z, v[7] = u1.w;
+                    } else {
+#pragma unroll
+                        for (int i = 0; i < 8; ++i) v[i] = xp[i];
+                    }
+                }
+                const bf16x8 b = frag8(v);
+#pragma unroll
+                for (int m = 0; m < 4; ++m) h1[m][t] = mma(w1[m][k], b, h1[m][t]);
+                if (TRAIN && f0 < kMlpIn) {
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) xt[(f0 + i) * kColStride + 16 * t + r] = b[i];
+                }
+            }
+        }
+#pragma unroll
+        for (int m = 0; m < 4; ++m) {
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) h1[m][t][i] = fmaxf(h1[m][t][i] + b1[m][i], 0.f);
+            }
+        }
+        put_rows(h1);
+        if (TRAIN) put_cols(h1t, h1);
+        lds_order();
+        // layer 2
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                const bf16x8 b = ld_frag(rm + (16 * t + r) * kRowStride + 32 * k + 8 * q);
+#pragma unroll
+                for (int m = 0; m < 4; ++m) h2[m][t] = mma(w2[m][k], b, h2[m][t]);
+            }
+        }
+#pragma unroll
+        for (int m = 0; m < 4; ++m) {
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) h2[m][t][i] = fmaxf(h2[m][t][i] + b2[m][i], 0.f);
+            }
+        }
+        lds_order();
+        put_rows(h2);
+        if (TRAIN) put_cols(h2t, h2);
+        lds_order();
+        // layer 3: lanes of q = 0 hold the three outputs of their row
+        bf16x8 dy[2];
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            f32x4 y = zero;
+#pragma unroll
+            for (int k = 0; k < 2; ++k)
+                y = mma(w3[k], ld_frag(rm + (16 * t + r) * kRowStride + 32 * k + 8 * q), y);
+            const int64_t row = row0 + 16 * t + r;
+            const float y0 = y[0] + b3[0], y1 = y[1] + b3[1], y2 = y[2] + b3[2];
+            const bool in = q == 0 && row < g.n;
+            if (!TRAIN) {
+                if (in) g.Y[3 * row] = y0, g.Y[3 * row + 1] = y1, g.Y[3 * row + 2] = y2;
+                continue;
+            }
+            // loss = mean_i (1 - cos(y_i, l_i)) and its gradient
+            float d[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+            if (in) {
+                const float l0 = g.L[3 * row], l1 = g.L[3 * row + 1], l2 = g.L[3 * row + 2];
+                const float yy = sqrtf(y0 * y0 + y1 * y1 + y2 * y2);
+                const float ll = sqrtf(l0 * l0 + l1 * l1 + l2 * l2);
+                float cs = 0.f;
+                if (yy > 0.f && ll > 0.f) {
+                    const float yl = y0 * l0 + y1 * l1 + y2 * l2;
+                    cs = yl / (yy * ll);
+                    // d cos / d y = l/(|y||l|) - (y.l) y / (|y|^3 |l|)
+                    const float a = 1.0f / (yy * ll), b = yl / (yy * yy * yy * ll);
+                    d[0] = -g.inv_n * (l0 * a - y0 * b);
+                    d[1] = -g.inv_n * (l1 * a - y1 * b);
+                    d[2] = -g.inv_n * (l2 * a - y2 * b);
+                }
+                loss += 1.0 - (double)cs;
+            }
+            dy[t] = frag8(d);
+            if (q == 0) {
+#pragma unroll
+                for (int o = 0; o < kMlpOut; ++o) {
+                    gb3[o] += d[o];
+                    yt[o * kColStride + 16 * t + r] = dy[t][o];
+                }
+            }
+        }
+        if constexpr (TRAIN) {
+            // back through layer 3 and the ReLUs
+            f32x4 d2[4][2], d1[4][2];
+#pragma unroll
+            for (int m = 0; m < 4; ++m) {
+#pragma unroll
+                for (int t = 0; t < 2; ++t) {
+                    d2[m][t] = mma(v3[m], dy[t], zero);
+                    d1[m][t] = zero;
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        if (!(h2[m][t][i] > 0.f)) d2[m][t][i] = 0.f;
+                        gb2[m][i] += d2[m][t][i];
+                    }
+                }
+            }
+            lds_order();
+            put_rows(d2);
+            put_cols(d2t, d2);
+            lds_order();
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+#pragma unroll
+                for (int k = 0; k < 2; ++k) {
+                    const bf16x8 b = ld_frag(rm + (16 * t + r) * kRowStride + 32 * k + 8 * q);
+#pragma unroll
+                    for (int m = 0; m < 4; ++m) d1[m][t] = mma(v2[m][k], b, d1[m][t]);
+                }
+            }
+#pragma unroll
+            for (int m = 0; m < 4; ++m) {
+#pragma unroll
+                for (int t = 0; t < 2; ++t) {
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        if (!(h1[m][t][i] > 0.f)) d1[m][t][i] = 0.f;
+                        gb1[m][i] += d1[m][t][i];
+                    }
+                }
+            }
+            put_cols(d1t, d1);
+            lds_order();
+            // the weight gradients: sums over the tile's 32 rows
+            bf16x8 fa[4], fb[4];
+#pragma unroll
+            for (int m = 0; m < 4; ++m) {
+                if (m < 3) fa[m] = ld_frag(xt + (16 * m + r) * kColStride + 8 * q);
+                fb[m] = ld_frag(d1t + (16 * m + r) * kColStride + 8 * q);
+            }
+#pragma unroll
+            for (int m = 0; m < 3; ++m) {
+#pragma unroll
+                for (int k = 0; k < 4; ++k) gw1[m][k] = mma(fa[m], fb[k], gw1[m][k]);
+            }
+#pragma unroll
+            for (int m = 0; m < 4; ++m) {
+                fa[m] = ld_frag(h1t + (16 * m + r) * kColStride + 8 * q);
+                fb[m] = ld_frag(d2t + (16 * m + r) * kColStride + 8 * q);
+            }
+#pragma unroll
+            for (int m = 0; m < 4; ++m) {
+#pragma unroll
+                for (int k = 0; k < 4; ++k) gw2[m][k] = mma(fa[m], fb[k], gw2[m][k]);
+            }
+            const bf16x8 fy = ld_frag(yt + r * kColStride + 8 * q);
+#pragma unroll
+            for (int m = 0; m < 4; ++m)
+                gw3[m] = mma(ld_frag(h2t + (16 * m + r) * kColStride + 8 * q), fy, gw3[m]);
+        }
+        lds_order();
+    }
+    if constexpr (TRAIN) {
+        // bias sums over the 16 rows of a lane group; the loss over the lanes
+#pragma unroll
+        for (int d = 8; d > 0; d >>= 1) {
+#pragma unroll
+            for (int m = 0; m < 4; ++m) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    gb1[m][i] += __shfl_xor(gb1[m][i], d, kWave);
+                    gb2[m][i] += __shfl_xor(gb2[m][i], d, kWave);
+                }
+            }
+#pragma unroll
+            for (int o = 0; o < kMlpOut; ++o) gb3[o] += __shfl_xor(gb3[o], d, kWave);
+            loss += __shfl_xor(loss, d, kWave);
+        }
+        if (lane == 0) lsum[wv] = loss;
+        // the workgroup's gradient: its wavefronts' in order
+        float *mine = (float *)work[wv];
+        lds_order();
+#pragma unroll
+        for (int m = 0; m < 4; ++m) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int in = 16 * m + 4 * q + i;
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    if (m < 3) mine[kOffW1 + in * kMlpHidden + 16 * k + r] = gw1[m][k][i];
+                    mine[kOffW2 + in * kMlpHidden + 16 * k + r] = gw2[m][k][i];
+                }
+                if (r < kMlpOut) mine[kOffW3 + in * kMlpOut + r] = gw3[m][i];
+                if (r == 0) {
+                    mine[kOffB1 + in] = gb1[m][i];
+                    mine[kOffB2 + in] = gb2[m][i];
+                }
+            }
+        }
+        if (lane == 0) {
+#pragma unroll
+            for (int o = 0; o < kMlpOut; ++o) mine[kOffB3 + o] = gb3[o];
+        }
         __syncthreads();
+        float *out = g.part + (int64_t)blockIdx.x * kMlpParams;
+        for (int i = tid; i < kMlpParams; i += kMlpWaves * kWave) {
+            float v = ((const float *)work[0])[i];
+#pragma unroll
+            for (int w = 1; w < kMlpWaves; ++w) v += ((const float *)work[w])[i];
+            out[i] = v;
+        }
+        if (tid == 0) {
+            double s = 0.0;
+            for (int w = 0; w < kMlpWaves; ++w) s += lsum[w];
+            g.lpart[blockIdx.x] = s;
+        }
     }
-    if (threadIdx.x == 0) part[blockIdx.x] = sh[0];
+}
+
+// grad[p] = the sum of the workgroups' partial gradients, in a fixed order:
+// four wavefronts of a workgroup take every fourth partial of 64 parameters.
+__global__ __launch_bounds__(256) void k_param_sum(const float *__restrict__ part, int count,
+                                                   float *__restrict__ grad) {
+    __shared__ float sh[4][kWave];
+    const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x / kWave;
+    const int p = blockIdx.x * kWave + lane;
+    float s = 0.f;
+    if (p < kMlpParams) {
+        constexpr int kUnroll = 16;
+        for (int w0 = wv; w0 < count; w0 += 4 * kUnroll) {
+            float v[kUnroll];
+#pragma unroll
+            for (int u = 0; u < kUnroll; ++u) {
+                // (beyond the last partial: the last one, not added)
+                const int w = w0 + 4 * u;
+                v[u] = part[(int64_t)(w < count ? w : count - 1) * kMlpParams + p];
+            }
+#pragma unroll
+            for (int u = 0; u < kUnroll; ++u)
+                if (w0 + 4 * u < count) s += v[u];
+        }
+    }
+    sh[wv][lane] = s;
+    __syncthreads();
+    if (wv == 0 && p < kMlpParams) grad[p] = ((s + sh[1][lane]) + sh[2][lane]) + sh[3][lane];
 }
 
 __global__ __launch_bounds__(256) void k_unit_rows(const float *__restrict__ Y, int64_t n,
@@ -170,56 +496,28 @@ __global__ __launch_bounds__(256) void k_adam(float *__restrict__ p, float *__re
 
 // ------------------------------------------------------------------ host --
 
-namespace {
-
-void gemm(hipStream_t st, const float *A, int64_t sam, int64_t sak, const float *B, int64_t sbk,
-          int64_t sbn, float *C, int64_t ldc, int M, int N, int K, const float *bias, bool relu,
-          const float *mask, int splits = 1, int64_t split_stride = 0) {
-    GemmArgs g;
-    g.A = A, g.sam = sam, g.sak = sak;
-    g.B = B, g.sbk = sbk, g.sbn = sbn;
-    g.C = C, g.ldc = ldc, g.split_stride = split_stride;
-    g.M = M, g.N = N, g.K = K;
-    int kps = (K + splits - 1) / splits;
-    kps = (kps + 31) / 32 * 32;
-    g.k_per_split = kps;
-    g.bias = bias, g.relu = relu ? 1 : 0, g.mask = mask;
-    const dim3 grid((unsigned)((M + 15) / 16), (unsigned)((N + 15) / 16), (unsigned)splits);
-    hipLaunchKernelGGL(k_gemm, grid, dim3(64), 0, st, g);
+static MlpArgs mlp_args(const float *P, const float *X, int64_t n) {
+    MlpArgs g;
+    memset(&g, 0, sizeof(g));
+    g.P = P;
+    g.X = X;
+    g.n = n;
+    g.aligned = ((uintptr_t)X & 15) == 0 ? 1 : 0;
+    return g;
 }
 
-// a weight gradient C (M x N, ldc = N) = A^T-like product with K = rows,
-// split over workgroups and summed in order
-hipError_t gemm_split(wnnc_ctx_s *ctx, const float *A, int64_t sam, int64_t sak, const float *B,
-                      int64_t sbk, int64_t sbn, float *C, int M, int N, int K) {
-    int splits = (K + 2047) / 2048;
-    if (splits > 512) splits = 512;
-    if (splits < 1) splits = 1;
-    const int64_t stride = (int64_t)M * N;
-    hipError_t e = ctx->mlp_part.ensure(stride * splits);
-    if (e != hipSuccess) return e;
-    gemm(ctx->stream, A, sam, sak, B, sbk, sbn, ctx->mlp_part.p, N, M, N, K, nullptr, false,
-         nullptr, splits, stride);
-    hipLaunchKernelGGL(k_split_sum, dim3((unsigned)((stride + 255) / 256)), dim3(256), 0,
-                       ctx->stream, ctx->mlp_part.p, splits, stride, stride, C);
-    return hipGetLastError();
+static int64_t mlp_wgs(int64_t n) {
+    const int64_t per = (int64_t)kMlpTile * kMlpWaves;
+    return (n + per - 1) / per;
 }
-
-}  // namespace
 
 hipError_t mlp_forward(wnnc_ctx_s *ctx, const float *P, const float *X, int64_t n, float *Y) {
-    hipStream_t st = ctx->stream;
-    hipError_t e = ctx->mlp_h1.ensure(n * kMlpHidden);
-    if (e == hipSuccess) e = ctx->mlp_h2.ensure(n * kMlpHidden);
-    if (e != hipSuccess) return e;
-    float *H1 = ctx->mlp_h1.p, *H2 = ctx->mlp_h2.p;
-    const int N = (int)n;
-    gemm(st, X, kMlpIn, 1, P + kOffW1, kMlpHidden, 1, H1, kMlpHidden, N, kMlpHidden, kMlpIn,
-         P + kOffB1, true, nullptr);
-    gemm(st, H1, kMlpHidden, 1, P + kOffW2, kMlpHidden, 1, H2, kMlpHidden, N, kMlpHidden,
-         kMlpHidden, P + kOffB2, true, nullptr);
-    gemm(st, H2, kMlpHidden, 1, P + kOffW3, kMlpOut, 1, Y, kMlpOut, N, kMlpOut, kMlpHidden,
-         P + kOffB3, false, nullptr);
+    MlpArgs g = mlp_args(P, X, n);
+    g.Y = Y;
+    // (three workgroups per CU fit the LDS)
+    const int64_t wgs = std::min<int64_t>(mlp_wgs(n), 3 * kMlpMaxWgs);
+    hipLaunchKernelGGL((k_mlp<false>), dim3((unsigned)wgs), dim3(kMlpWaves * kWave), 0, ctx->stream,
+                       g);
     return hipGetLastError();
 }
 
@@ -232,44 +530,23 @@ hipError_t mlp_normals(wnnc_ctx_s *ctx, const float *Y, int64_t n, float *out) {
 hipError_t mlp_loss_grad(wnnc_ctx_s *ctx, const float *P, const float *X, const float *L,
                          int64_t n, float *grad, double *loss) {
     hipStream_t st = ctx->stream;
-    hipError_t e = ctx->mlp_y.ensure(n * kMlpOut);
-    if (e == hipSuccess) e = ctx->mlp_dy.ensure(n * kMlpOut);
-    if (e == hipSuccess) e = ctx->mlp_d2.ensure(n * kMlpHidden);
-    if (e == hipSuccess) e = ctx->mlp_d1.ensure(n * kMlpHidden);
-    const int64_t nb = (n + 255) / 256;
-    if (e == hipSuccess) e = ctx->mlp_lpart.ensure(nb);
+    const int64_t wgs = std::min<int64_t>(mlp_wgs(n), kMlpMaxWgs);
+    hipError_t e = ctx->mlp_part.ensure(wgs * kMlpParams);
+    if (e == hipSuccess) e = ctx->mlp_lpart.ensure(wgs);
     if (e != hipSuccess) return e;
-    e = mlp_forward(ctx, P, X, n, ctx->mlp_y.p);
-    if (e != hipSuccess) return e;
-    float *H1 = ctx->mlp_h1.p, *H2 = ctx->mlp_h2.p, *Y = ctx->mlp_y.p, *dY = ctx->mlp_dy.p;
-    float *D2 = ctx->mlp_d2.p, *D1 = ctx->mlp_d1.p;
-    const int N = (int)n;
-    hipLaunchKernelGGL(k_cos_loss, dim3((unsigned)nb), dim3(256), 0, st, Y, L, n, 1.0f / (float)n,
-                       dY, ctx->mlp_lpart.p);
-    // layer 3: dW3 = H2^T dY, db3 = colsum dY, dH2 = (dY W3^T) * [H2 > 0]
-    e = gemm_split(ctx, H2, 1, kMlpHidden, dY, kMlpOut, 1, grad + kOffW3, kMlpHidden, kMlpOut, N);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_colsum, dim3(kMlpOut), dim3(256), 0, st, dY, n, kMlpOut, grad + kOffB3);
-    gemm(st, dY, kMlpOut, 1, P + kOffW3, 1, kMlpOut, D2, kMlpHidden, N, kMlpHidden, kMlpOut,
-         nullptr, false, H2);
-    // layer 2
-    e = gemm_split(ctx, H1, 1, kMlpHidden, D2, kMlpHidden, 1, grad + kOffW2, kMlpHidden,
-                   kMlpHidden, N);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_colsum, dim3(kMlpHidden), dim3(256), 0, st, D2, n, kMlpHidden,
-                       grad + kOffB2);
-    gemm(st, D2, kMlpHidden, 1, P + kOffW2, 1, kMlpHidden, D1, kMlpHidden, N, kMlpHidden,
-         kMlpHidden, nullptr, false, H1);
-    // layer 1
-    e = gemm_split(ctx, X, 1, kMlpIn, D1, kMlpHidden, 1, grad + kOffW1, kMlpIn, kMlpHidden, N);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_colsum, dim3(kMlpHidden), dim3(256), 0, st, D1, n, kMlpHidden,
-                       grad + kOffB1);
+    MlpArgs g = mlp_args(P, X, n);
+    g.L = L;
+    g.part = ctx->mlp_part.p;
+    g.lpart = ctx->mlp_lpart.p;
+    g.inv_n = 1.0f / (float)n;
+    hipLaunchKernelGGL((k_mlp<true>), dim3((unsigned)wgs), dim3(kMlpWaves * kWave), 0, st, g);
+    hipLaunchKernelGGL(k_param_sum, dim3((kMlpParams + kWave - 1) / kWave), dim3(256), 0, st,
+                       ctx->mlp_part.p, (int)wgs, grad);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (loss) {
-        std::vector<double> lp((size_t)nb);
-        e = hipMemcpyAsync(lp.data(), ctx->mlp_lpart.p, (size_t)nb * sizeof(double),
+        std::vector<double> lp((size_t)wgs);
+        e = hipMemcpyAsync(lp.data(), ctx->mlp_lpart.p, (size_t)wgs * sizeof(double),
                            hipMemcpyDeviceToHost, st);
         if (e == hipSuccess) e = hipStreamSynchronize(st);
         if (e != hipSuccess) return e;
