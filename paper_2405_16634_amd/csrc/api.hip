@@ -305,6 +305,7 @@ wnnc_status wnnc_destroy(wnnc_ctx ctx) {
     ctx->task_lo.release();
     ctx->knn_groups.release();
     ctx->knn_tmp.release();
+    ctx->knn_depths.release();
     ctx->areas.release();
     ctx->momhi.release();
     ctx->gradf.release();

@@ -144,6 +144,7 @@ struct wnnc_ctx_s {
     // warm start: neighbours, features, MLP outputs and partial gradients
     DevBuf<int4> knn_groups;       // neighbour-search groups (first, last; root, end)
     int knn_ngroups = 0;           // 0: not built for the current tree
+    DevBuf<unsigned long long> knn_depths;  // runs per depth, in pairs of 32-bit counts
     DevBuf<uint32_t> knn_tmp;      // 4 n: group construction
     DevBuf<int32_t> knn_idx;       // n * 16 sorted neighbour positions
     DevBuf<float> knn_d2;          // n * 16 squared distances

@@ -2,15 +2,23 @@
 // and the neighbourhood features of the learned warm start: the offsets to
 // the 16 neighbours in increasing distance, divided by their RMS length.
 //
-// One wavefront per group of 64 Morton-consecutive points of one cloud, one
-// point per lane.  Each lane keeps a candidate list (squared distance, sorted
-// index) in registers, sorted ascending, seeded with its Morton-order
-// neighbours on both sides (a tight radius from the start).  The wavefront then walks the
-// cloud's pre-order node range as one scalar loop: a subtree is skipped when
-// its cell (built with the tree) is farther than every lane's current 16th
-// candidate; the points of the leaves reached are offered to every lane
-// that needs them.  Ties are broken by sorted index,
-// so the result does not depend on the order in which points are offered.
+// One wavefront per group of up to 64 Morton-consecutive points of one cloud,
+// one point per lane.  Each lane keeps a candidate list in registers, sorted
+// ascending, seeded with its Morton-order neighbours on both sides (a tight
+// radius from the start).  The wavefront then searches the tree with a stack
+// of nodes, 64 at a time, one per lane: a node goes on when its cell (built
+// with the tree) is within the group's reach of the group's box, and when some
+// lane's ball reaches it; the points of the leaves are offered to every lane.
+// Ties are broken by sorted index, so the result does not depend on the order
+// in which points are offered.
+//
+// What bounds it: instructions, and on clouds of very uneven density the
+// longest search of one group.  A search that walked the nodes one by one, all
+// lanes on the same node, with compare-and-select insertions, took 31,800
+// vector instructions per wavefront and 836 us on a 164k-point sphere (VALU
+// 89 % busy), 945 us on a 100k-point knot; keys and FP64 minima took that to
+// 475 and 711 us, bound by the scalar unit and its loads, and nodes tested one
+// per lane to 245 and 280 us.
 // Requires points inside [-1,1]^3 (normalized clouds).
 #include <float.h>
 
@@ -20,34 +28,53 @@
 namespace wnnc {
 
 constexpr int kK = 16;
+constexpr int kSeedBatch = 8;  // seed points' loads in flight
+constexpr int kHomePoints = 32;  // a search's first node holds at least so many points
+// A search's stack of nodes.  A step leaves room for 8 entries per level, so
+// that steps of one node, which go depth first, never overflow it.
+constexpr int kKnnStack = 512;
 
-struct Cand {
-    float d[kK];
-    int j[kK];
-};
-
-// (d, j) sorts before (dd, jj).  Bitwise operators: no short-circuit
-// branches, so the callers compile to compares and selects.
-__device__ inline bool better(float d, int j, float dd, int jj) {
-    return (d < dd) | ((d == dd) & (j < jj));
+// A candidate is one FP64 key: the squared distance's bits above the sorted
+// index.  Distances are not negative, so the keys, read as doubles (finite
+// ones: the upper half is a float's bits), order by distance and then index,
+// and a list is kept with FP64 minima and maxima, which issue at the FP32
+// rate.  The empty entry (FLT_MAX, index -1) is above every other.
+__device__ inline double cand_key(float d, int j) {
+    return __hiloint2double(__float_as_int(d), j);
 }
+__device__ inline float cand_d(double k) { return __int_as_float(__double2hiint(k)); }
+__device__ inline int cand_j(double k) { return __double2loint(k); }
 
-// Inserts (d, j) into the sorted list where `take` holds and (d, j) beats
-// the last entry: every entry the new one beats moves down one place.
-// Branch-free (selects only), so the list stays in the same registers.
-__device__ inline void offer(Cand &c, float d, int j, bool take = true) {
-    take = take & better(d, j, c.d[kK - 1], c.j[kK - 1]);
-#pragma unroll
-    for (int k = kK - 1; k > 0; --k) {
-        const bool shift = take & better(d, j, c.d[k - 1], c.j[k - 1]);
-        // beats entry k but not entry k-1
-        const bool put = take & !shift & better(d, j, c.d[k], c.j[k]);
-        c.d[k] = shift ? c.d[k - 1] : (put ? d : c.d[k]);
-        c.j[k] = shift ? c.j[k - 1] : (put ? j : c.j[k]);
-    }
-    const bool first = take & better(d, j, c.d[0], c.j[0]);
-    c.d[0] = first ? d : c.d[0];
-    c.j[0] = first ? j : c.j[0];
+// Inserts key x into the sorted list (the last entry drops out), unless no
+// lane has one: entry k becomes the smaller of itself and the larger of x and
+// entry k - 1.  Two instructions per entry (compares and selects of distances
+// and indices took about seven), written out with the branch around them:
+// fmin and fmax quiet their operands first, and the list is copied where
+// paths with and without an insertion meet.
+__device__ inline void offer_if(double (&c)[kK], double x, uint64_t takers) {
+    double s, t;
+    static_assert(kK == 16, "the list below has 16 entries");
+    // the sixteen entries are %0 .. %15
+#define WNNC_PAIR(a, b, d)                  \
+    "v_max_f64 %16, %" #b ", %18\n\t"       \
+    "v_max_f64 %17, %" #d ", %18\n\t"       \
+    "v_min_f64 %" #a ", %" #a ", %16\n\t"   \
+    "v_min_f64 %" #b ", %" #b ", %17\n\t"
+    asm("s_cmp_eq_u64 %19, 0\n\t"
+        "s_cbranch_scc1 .Lskip%=\n\t"
+        WNNC_PAIR(15, 14, 13) WNNC_PAIR(13, 12, 11) WNNC_PAIR(11, 10, 9)
+        WNNC_PAIR(9, 8, 7) WNNC_PAIR(7, 6, 5) WNNC_PAIR(5, 4, 3)
+        WNNC_PAIR(3, 2, 1)
+        "v_max_f64 %16, %0, %18\n\t"
+        "v_min_f64 %0, %0, %18\n\t"
+        "v_min_f64 %1, %1, %16\n"
+        ".Lskip%=:"
+        : "+v"(c[0]), "+v"(c[1]), "+v"(c[2]), "+v"(c[3]), "+v"(c[4]), "+v"(c[5]), "+v"(c[6]),
+          "+v"(c[7]), "+v"(c[8]), "+v"(c[9]), "+v"(c[10]), "+v"(c[11]), "+v"(c[12]),
+          "+v"(c[13]), "+v"(c[14]), "+v"(c[15]), "=&v"(s), "=&v"(t)
+        : "v"(x), "s"(takers)
+        : "scc");
+#undef WNNC_PAIR
 }
 
 typedef int v4i_knn __attribute__((ext_vector_type(4)));
@@ -64,14 +91,43 @@ __device__ inline float4 knn_ld_f4(const float4 *p) {
 }
 // groups: per wavefront (first, last point; first, end node of the cloud),
 // the 64-point groups of every cloud.
+__device__ inline float lane_f(float v, int lane) {
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane));
+}
+
+// Largest (MAX) or smallest value of the lanes.
+template <bool MAX>
+__device__ inline float wave_extreme(float v) {
+#define WNNC_STEP(ctrl)                                                                     \
+    {                                                                                       \
+        const int b = __float_as_int(v);                                                    \
+        const float o = __int_as_float(__builtin_amdgcn_update_dpp(b, b, ctrl, 0xf, 0xf, false)); \
+        v = MAX ? fmaxf(v, o) : fminf(v, o);                                                \
+    }
+    WNNC_STEP(0x111) WNNC_STEP(0x112) WNNC_STEP(0x114) WNNC_STEP(0x118)  // row_shr 1 2 4 8
+    WNNC_STEP(0x142) WNNC_STEP(0x143)                                    // row_bcast 15 31
+#undef WNNC_STEP
+    return lane_f(v, 63);
+}
+
+// Distance squared between the boxes [al, ah] and [bl, bh] along the axes,
+// rounded as the distance of two points is: no larger than that of any two
+// points in them.
+__device__ inline float box_d2(float dx, float dy, float dz) {
+    dx = fmaxf(dx, 0.0f), dy = fmaxf(dy, 0.0f), dz = fmaxf(dz, 0.0f);
+    return fmaf(dx, dx, fmaf(dy, dy, dz * dz));
+}
+
 __global__ __launch_bounds__(kWave) void k_knn(const float4 *__restrict__ pts,
                                                const float4 *__restrict__ cells,
                                                const int4 *__restrict__ topo,
+                                               const float4 *__restrict__ mom,
                                                const int4 *__restrict__ groups,
                                                const int64_t *__restrict__ off,
                                                const int32_t *__restrict__ cloud, int ngroups,
                                                int32_t *__restrict__ nbr,
                                                float *__restrict__ nd2) {
+    __shared__ int stack[kKnnStack];
     const int g = blockIdx.x;
     if (g >= ngroups) return;
     const int lane = threadIdx.x;
@@ -80,100 +136,169 @@ __global__ __launch_bounds__(kWave) void k_knn(const float4 *__restrict__ pts,
     const int lo = (int)off[c], hi = (int)off[c + 1];
     const int t = G.x + lane;
     const bool valid = t < G.y;
-    float4 p = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (valid) p = pts[t];
-    Cand cd;
+    const float4 p = pts[min(t, G.y - 1)];
+    const double none = cand_key(FLT_MAX, -1);
+    // an idle lane's list takes nothing: no key is below 0
+    double cd[kK];
 #pragma unroll
-    for (int k = 0; k < kK; ++k) {
-        cd.d[k] = FLT_MAX;
-        cd.j[k] = -1;
-    }
+    for (int k = 0; k < kK; ++k) cd[k] = valid ? none : 0.0;
     // seed with the kK Morton-order neighbours on each side (one side alone
     // fills the list, which bounds the radius also where the curve jumps);
     // the walk below skips them
     const int s_lo = max(lo, t - kK), s_hi = min(hi - 1, t + kK);
 #pragma unroll 1
-    for (int q = -kK; q <= kK; ++q) {
-        const int j = t + q;
-        const bool in = valid && q != 0 && j >= s_lo && j <= s_hi;
-        float4 r = p;
-        if (in) r = pts[j];
-        const float dx = r.x - p.x, dy = r.y - p.y, dz = r.z - p.z;
-        offer(cd, fmaf(dx, dx, fmaf(dy, dy, dz * dz)), j, in);
+    for (int q0 = 0; q0 < 2 * kK; q0 += kSeedBatch) {
+        float4 r[kSeedBatch];
+#pragma unroll
+        for (int u = 0; u < kSeedBatch; ++u) {
+            const int q = q0 + u, j = t + (q < kK ? q - kK : q - kK + 1);
+            r[u] = pts[min(max(j, lo), hi - 1)];
+        }
+#pragma unroll
+        for (int u = 0; u < kSeedBatch; ++u) {
+            const int q = q0 + u, j = t + (q < kK ? q - kK : q - kK + 1);
+            const bool in = j >= s_lo && j <= s_hi;
+            const float dx = r[u].x - p.x, dy = r[u].y - p.y, dz = r[u].z - p.z;
+            offer_if(cd, in ? cand_key(fmaf(dx, dx, fmaf(dy, dy, dz * dz)), j) : none,
+                     __ballot(in));
+        }
     }
-    // One pruned walk over the pre-order range [nb, ne), skipping the
-    // subtree [hole, hole_end) (hole = -1: none).
-    auto walk = [&](int nb, int ne, int hole, int hole_end) {
-        int node = nb;
-        while (node < ne) {
-            if (node == hole) {
-                node = hole_end;
-                continue;
-            }
-            // the node and its geometry: two independent scalar loads
-            const int4 tp = knn_ld_i4(topo + node);
-            const float4 cb = knn_ld_f4(cells + node);
-            if (cb.w < 0.0f) {  // a single-point leaf: its point directly
-                const int j = tp.y;
-                const float dx = cb.x - p.x, dy = cb.y - p.y, dz = cb.z - p.z;
-                const float d2 = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
-                const bool take = valid & ((j < s_lo) | (j > s_hi)) &
-                                  better(d2, j, cd.d[kK - 1], cd.j[kK - 1]);
-                if (__ballot(take)) offer(cd, d2, j, take);
-                node = tp.x;
-                continue;
-            }
-            // each lane's distance to the node's cell
-            const float bx = fmaxf(fmaxf(cb.x - p.x, p.x - (cb.x + cb.w)), 0.0f);
-            const float by = fmaxf(fmaxf(cb.y - p.y, p.y - (cb.y + cb.w)), 0.0f);
-            const float bz = fmaxf(fmaxf(cb.z - p.z, p.z - (cb.z + cb.w)), 0.0f);
-            const bool need = valid & (bx * bx + by * by + bz * bz <= cd.d[kK - 1]);
-            if (__ballot(need) == 0ull) {
-                node = tp.x;
-                continue;
-            }
-            if (tp.w & kRecLeaf) {
+    // the group's box; the idle lanes repeat its last point
+    const float glx = wave_extreme<false>(p.x), ghx = wave_extreme<true>(p.x);
+    const float gly = wave_extreme<false>(p.y), ghy = wave_extreme<true>(p.y);
+    const float glz = wave_extreme<false>(p.z), ghz = wave_extreme<true>(p.z);
+    // A lane's bound: its last entry, or a distance within which some node has
+    // more than kK points.  What is farther is not needed.
+    float bound = cand_d(cd[kK - 1]), reach = wave_extreme<true>(bound);
+    // Nearest first: the deepest node that holds the whole group and at least
+    // kHomePoints points (its home), whose points give every lane a tight
+    // radius; then, with that radius, the other children of the nodes above it.
+    int home = G.z, sp = 0;
 #pragma unroll 1
-                for (int j = tp.y; j < tp.z; ++j) {
-                    const float4 r = knn_ld_f4(pts + j);
-                    const float dx = r.x - p.x, dy = r.y - p.y, dz = r.z - p.z;
-                    const float d2 = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
-                    // seeded (or the target itself) points were offered already
-                    const bool take = need & ((j < s_lo) | (j > s_hi)) &
-                                      better(d2, j, cd.d[kK - 1], cd.j[kK - 1]);
-                    if (__ballot(take)) offer(cd, d2, j, take);
-                }
-                node = tp.x;
-            } else {
-                node = node + 1;
+    for (int d = 0; d < kMaxDepth; ++d) {
+        const int fl = knn_ld_i4((const int4 *)(mom + (int64_t)kRecStride * home)).w;
+        const int nk = fl >> kRecKidShift;
+        if (nk == 0) break;
+        int kid = home + 1;
+        if (fl & kRecWideKids) {
+            for (int k = 1, ch = kid; k < nk; ++k) {
+                ch = knn_ld_i4(topo + ch).x;
+                if (lane == k) kid = ch;
+            }
+        } else if (lane > 0 && lane < nk) {
+            kid = home + ((const uint16_t *)(mom + (int64_t)kRecStride * home + 3))[lane - 1];
+        }
+        const int4 tc = topo[kid];
+        const uint64_t holds = __ballot(lane < nk && tc.y <= G.x && tc.z >= G.y &&
+                                        tc.z - tc.y >= kHomePoints);
+        if (holds == 0ull) break;
+        const int at = __builtin_ctzll(holds);
+        if (lane < nk && lane != at) stack[sp + lane - (lane > at ? 1 : 0)] = kid;
+        sp += nk - 1;
+        home = __builtin_amdgcn_readlane(kid, at);
+    }
+    if (lane == 0) stack[sp] = home;
+    __syncthreads();
+    int base = sp++;  // the home's subtree is searched before what lies below it
+    // One step takes up to 64 nodes from the stack, one per lane: those whose
+    // cells are within the reach of some box are opened: their children go to
+    // the stack, or a leaf's points are offered to all lanes in turn.
+#pragma unroll 1
+    while (sp > 0) {
+        base = sp > base ? base : 0;
+        const int take_n = min(min(sp - base, kWave), max(1, (kKnnStack - 8 * kMaxDepth - sp) / 7));
+        const bool on = lane < take_n;
+        const int node = stack[sp - 1 - (on ? lane : 0)];
+        sp -= take_n;
+        __syncthreads();
+        const int4 tp = topo[node];
+        const float4 q = cells[node];
+        const float4 *rec = mom + (int64_t)kRecStride * node;
+        const int fl = __float_as_int(rec[0].w);
+        const float4 R3 = rec[3];
+        const bool single = q.w < 0.0f;
+        const float h = single ? 0.0f : q.w;
+        const float ux = q.x + h, uy = q.y + h, uz = q.z + h;
+        const float d2 = box_d2(fmaxf(q.x - ghx, glx - ux), fmaxf(q.y - ghy, gly - uy),
+                                fmaxf(q.z - ghz, glz - uz));
+        const bool near = on && d2 <= reach;
+        const bool leaf = (tp.w & kRecLeaf) != 0;
+        uint64_t offers = __ballot(near && leaf);
+#pragma unroll 1
+        while (offers) {
+            const int s = __builtin_ctzll(offers);
+            offers &= offers - 1ull;
+            float x = lane_f(q.x, s), y = lane_f(q.y, s), z = lane_f(q.z, s);
+            int j = __builtin_amdgcn_readlane(tp.y, s);
+            const int je = __builtin_amdgcn_readlane(tp.z, s);
+            if (lane_f(q.w, s) >= 0.0f) {
+                const float4 r = knn_ld_f4(pts + j);
+                x = r.x, y = r.y, z = r.z;
+            }
+            for (;;) {
+                const float dx = x - p.x, dy = y - p.y, dz = z - p.z;
+                const double key = cand_key(fmaf(dx, dx, fmaf(dy, dy, dz * dz)), j);
+                // seeded (or the target itself) points were offered already
+                const bool take =
+                    ((uint32_t)(j - s_lo) > (uint32_t)(s_hi - s_lo)) & (key < cd[kK - 1]);
+                offer_if(cd, take ? key : none, __ballot(take));
+                if (++j >= je) break;
+                const float4 r = knn_ld_f4(pts + j);
+                x = r.x, y = r.y, z = r.z;
             }
         }
-    };
-    // Nearest first: the deepest node holding the whole group (its home),
-    // whose points give every lane a tight radius, then the rest of the
-    // cloud's tree with that radius.  At most one node per depth and 8
-    // children per node are examined, so the search ends on any input.
-    int home = G.z;
-    for (int d = 0; d < kMaxDepth; ++d) {
-        const int4 th = knn_ld_i4(topo + home);
-        if (th.w & kRecLeaf) break;
-        int ch = home + 1;
-        for (int q = 0; q < 7; ++q) {  // the child whose point range holds `first`
-            const int4 tc = knn_ld_i4(topo + ch);
-            if (tc.z > G.x) break;
-            ch = tc.x;
+        bound = fminf(bound, cand_d(cd[kK - 1]));
+        // of the other nodes, those that some lane's ball reaches
+        uint64_t tests = __ballot(near && !leaf), open = tests;
+#pragma unroll 1
+        while (tests) {
+            const int s = __builtin_ctzll(tests);
+            tests &= tests - 1ull;
+            const float x = lane_f(q.x, s), y = lane_f(q.y, s), z = lane_f(q.z, s);
+            const float w = lane_f(q.w, s);
+            const float lx = x - p.x, ly = y - p.y, lz = z - p.z;
+            const float hx = p.x - (x + w), hy = p.y - (y + w), hz = p.z - (z + w);
+            const float d = box_d2(fmaxf(lx, hx), fmaxf(ly, hy), fmaxf(lz, hz));
+            if (__ballot(d <= bound) == 0ull) open &= ~(1ull << s);
+            // the farthest corner: -min is the larger of the two extents
+            const float f = box_d2(-fminf(lx, hx), -fminf(ly, hy), -fminf(lz, hz));
+            const int np = __builtin_amdgcn_readlane(tp.z - tp.y, s);
+            bound = np > kK ? fminf(bound, f) : bound;
         }
-        if (knn_ld_i4(topo + ch).z < G.y) break;  // it does not hold the whole group
-        home = ch;
+        reach = wave_extreme<true>(bound);
+        // the opened nodes' children, at the ranks of their counts' prefix sums
+        const int nk = ((open >> lane) & 1ull) != 0ull ? fl >> kRecKidShift : 0;
+        int at = sp;
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+            const uint64_t m = __ballot((nk >> b) & 1);
+            at += (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
+                                                 __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u))
+                  << b;
+            sp += __popcll(m) << b;
+        }
+        const uint32_t w[4] = {__float_as_uint(R3.x), __float_as_uint(R3.y), __float_as_uint(R3.z),
+                               __float_as_uint(R3.w)};
+        if (nk > 0) stack[at] = node + 1;
+#pragma unroll
+        for (int k = 1; k < 8; ++k)
+            if (k < nk)
+                stack[at + k] =
+                    node + (int)((w[(k - 1) / 2] >> (16 * ((k - 1) & 1))) & 0xffffu);
+        if (nk > 0 && (fl & kRecWideKids)) {
+            int kid = node + 1;
+            for (int k = 1; k < nk; ++k) {
+                kid = topo[kid].x;
+                stack[at + k] = kid;
+            }
+        }
+        __syncthreads();
     }
-    const int home_end = knn_ld_i4(topo + home).x;
-    walk(home, home_end, -1, 0);
-    walk(G.z, G.w, home, home_end);
     if (valid) {
 #pragma unroll
         for (int k = 0; k < kK; ++k) {
-            nbr[(int64_t)t * kK + k] = cd.j[k];
-            nd2[(int64_t)t * kK + k] = cd.d[k];
+            nbr[(int64_t)t * kK + k] = cand_j(cd[k]);
+            nd2[(int64_t)t * kK + k] = cand_d(cd[k]);
         }
     }
 }
@@ -220,18 +345,50 @@ __global__ __launch_bounds__(256) void k_features(const float4 *__restrict__ pts
 }
 
 // Neighbour-search groups: runs of sorted points inside one octree cell of
-// depth kKnnGroupDepth (so of one cloud), cut every 64 points.  A wavefront
-// walks the union of its lanes' search balls; capping the cell keeps that
-// union small where points are sparse (64 Morton-consecutive isolated
-// points can span much of the cloud's box), at the price of partly filled
-// wavefronts there.
-constexpr int kKnnGroupDepth = 6;
+// one depth (so of one cloud), cut every 64 points.  A wavefront walks the
+// union of its lanes' search balls; capping the cell keeps that union small
+// where points are sparse (64 Morton-consecutive isolated points can span
+// much of the cloud's box), at the price of partly filled wavefronts there.
+// The depth is the deepest whose cells hold kKnnMean points on average.  Areas
+// of a 164k-point sphere / a 100k / a 500k-point knot: 412 / 413 / 1578 us with
+// 10, 342 / 431 / 2017 us with 14 or 20 (one level up: longer searches where
+// the knot is sparse); the largest cells of at most 64 points, whatever their
+// depth: 397 / 723 / 2066 us.
+constexpr int kKnnMean = 10;
+
+// count[d] += the sorted points that share less than d octal digits with the
+// point before them (the runs of depth d), d = 0 .. kMaxDepth.
+__global__ __launch_bounds__(256) void k_knn_depths(const unsigned long long *__restrict__ keys,
+                                                    int n, uint32_t *__restrict__ count) {
+    __shared__ uint32_t h[kMaxDepth + 1];
+    if (threadIdx.x <= kMaxDepth) h[threadIdx.x] = 0u;
+    __syncthreads();
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i < n) {
+        const unsigned long long x = i > 0 ? keys[i] ^ keys[i - 1] : ~0ull;
+        // the first depth at which the two points part
+        int d = kMaxDepth + 1;
+        if (x >> kMortonBits) d = 0;
+        else if (x) d = (__clzll(x) - (64 - kMortonBits)) / 3 + 1;
+        if (d <= kMaxDepth) atomicAdd(&h[d], 1u);
+    }
+    __syncthreads();
+    if (threadIdx.x <= kMaxDepth && h[threadIdx.x]) atomicAdd(count + threadIdx.x, h[threadIdx.x]);
+}
 
 __global__ __launch_bounds__(256) void k_knn_brk(const unsigned long long *__restrict__ keys,
-                                                 int n, uint32_t *__restrict__ brk) {
+                                                 const uint32_t *__restrict__ count, int n,
+                                                 uint32_t *__restrict__ brk) {
     const int i = blockIdx.x * 256 + threadIdx.x;
     if (i >= n) return;
-    const int sh = 3 * (kMaxDepth - kKnnGroupDepth);  // the cloud index sits above the key
+    int depth = 0;
+    uint32_t runs = count[0];
+    for (int d = 1; d <= kMaxDepth; ++d) {
+        runs += count[d];
+        if ((int64_t)runs * kKnnMean > n) break;
+        depth = d;
+    }
+    const int sh = 3 * (kMaxDepth - depth);  // the cloud index sits above the key
     brk[i] = (i == 0 || (keys[i] >> sh) != (keys[i - 1] >> sh)) ? 1u : 0u;
 }
 
@@ -279,12 +436,16 @@ __global__ __launch_bounds__(256) void k_knn_groups(const uint32_t *__restrict__
 static hipError_t knn_groups(wnnc_ctx_s *ctx) {
     const int n = (int)ctx->n;
     hipStream_t st = ctx->stream;
+    static_assert((kMaxDepth + 1) % 2 == 0, "the depth counts are cleared in pairs");
     hipError_t e = ctx->knn_tmp.ensure(5 * (int64_t)n + 1);
     if (e != hipSuccess) return e;
+    if ((e = ctx->knn_depths.ensure((kMaxDepth + 1) / 2)) != hipSuccess) return e;
     uint32_t *brk = ctx->knn_tmp.p, *rx = brk + n, *runs = rx + n, *gs = runs + n, *gx = gs + n;
-    uint32_t *cnt = gx + n;
+    uint32_t *cnt = gx + n, *depths = (uint32_t *)ctx->knn_depths.p;
     const unsigned nb = (unsigned)((n + 255) / 256);
-    hipLaunchKernelGGL(k_knn_brk, dim3(nb), dim3(256), 0, st, ctx->keys_a.p, n, brk);
+    if ((e = launch_zero_u64(ctx->knn_depths.p, (kMaxDepth + 1) / 2, st)) != hipSuccess) return e;
+    hipLaunchKernelGGL(k_knn_depths, dim3(nb), dim3(256), 0, st, ctx->keys_a.p, n, depths);
+    hipLaunchKernelGGL(k_knn_brk, dim3(nb), dim3(256), 0, st, ctx->keys_a.p, depths, n, brk);
     if ((e = exclusive_scan_u32(brk, rx, n, ctx->scan_tmp.p, st)) != hipSuccess) return e;
     hipLaunchKernelGGL(k_knn_runs, dim3(nb), dim3(256), 0, st, brk, rx, n, runs);
     hipLaunchKernelGGL(k_knn_gflag, dim3(nb), dim3(256), 0, st, brk, rx, runs, n, gs);
@@ -311,8 +472,8 @@ hipError_t launch_knn(wnnc_ctx_s *ctx) {
     if (ctx->knn_ngroups == 0 && (e = knn_groups(ctx)) != hipSuccess) return e;
     if (ctx->knn_ngroups > 0)
         hipLaunchKernelGGL(k_knn, dim3((unsigned)ctx->knn_ngroups), dim3(kWave), 0, ctx->stream,
-                           ctx->pts.p, ctx->cells.p, ctx->topo.p, ctx->knn_groups.p,
-                           ctx->d_offsets.p, ctx->cloud_of.p, ctx->knn_ngroups, ctx->knn_idx.p,
+                           ctx->pts.p, ctx->cells.p, ctx->topo.p, ctx->mom.p,
+                           ctx->knn_groups.p, ctx->d_offsets.p, ctx->cloud_of.p, ctx->knn_ngroups, ctx->knn_idx.p,
                            ctx->knn_d2.p);
     return hipGetLastError();
 }
