@@ -167,78 +167,148 @@ __global__ __launch_bounds__(256) void k_point_cloud(const unsigned long long *_
 }
 
 // ------------------------------------------------------------ radix sort --
-// Stable LSD radix sort of (45-bit key, uint32 value), 8 bits per pass.
+// Stable LSD radix sort of (45-bit key, uint32 value), 9 bits per pass: the
+// 45 bits take five passes of three kernels (a tile's digit counts, their
+// prefix sums over the tiles, the scatter).  It is bound by the latency of
+// its launches and barriers, not by its 24 bytes per key and pass.  With 8
+// bits, six passes of five kernels (the counts scanned as one array) and a
+// barrier after every 256 keys, sorting 262k query points took 147 us; this
+// takes 65 us, and a build 1060 -> 610 us at 100k points, 2142 -> 1040 us at
+// 500k (of which the walks planned on the device are part).
 
-constexpr int kRsThreads = 256;
-constexpr int kRsItems = 8;
+constexpr int kRsBits = 9;
+constexpr int kRsBins = 1 << kRsBits;
+constexpr int kRsThreads = kRsBins;  // one thread per digit
+constexpr int kRsWaves = kRsThreads / kWave;
+constexpr int kRsItems = 4;  // keys per thread; 2 and 8 build as fast at 2k to 3M points
 constexpr int kRsTile = kRsThreads * kRsItems;
+
+static inline int rs_tiles(int64_t n) { return (int)((n + kRsTile - 1) / kRsTile); }
+
+int rs_passes(int key_bits) { return (key_bits + kRsBits - 1) / kRsBits; }
+
+// Inclusive prefix sum over the wavefront's lanes.
+__device__ inline uint32_t wave_scan_u32(uint32_t v, int lane) {
+#pragma unroll
+    for (int d = 1; d < kWave; d <<= 1) {
+        const uint32_t o = __shfl_up(v, d);
+        v += lane >= d ? o : 0u;
+    }
+    return v;
+}
 
 __global__ __launch_bounds__(kRsThreads) void k_rs_hist(const unsigned long long *__restrict__ keys,
                                                         int64_t n, int shift,
                                                         uint32_t *__restrict__ hist, int ntiles) {
-    __shared__ uint32_t h[256];
+    __shared__ uint32_t h[kRsBins];
     h[threadIdx.x] = 0;
-    __syncthreads();
     const int64_t base = (int64_t)blockIdx.x * kRsTile;
+    unsigned long long key[kRsItems];
 #pragma unroll
     for (int k = 0; k < kRsItems; ++k) {
-        int64_t i = base + k * kRsThreads + threadIdx.x;
-        if (i < n) atomicAdd(&h[(unsigned)(keys[i] >> shift) & 255u], 1u);
+        const int64_t i = base + k * kRsThreads + threadIdx.x;
+        key[k] = i < n ? keys[i] : 0ull;
     }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kRsItems; ++k)
+        if (base + k * kRsThreads + threadIdx.x < n)
+            atomicAdd(&h[(unsigned)(key[k] >> shift) & (kRsBins - 1)], 1u);
     __syncthreads();
     hist[(int64_t)threadIdx.x * ntiles + blockIdx.x] = h[threadIdx.x];
 }
 
+// One wavefront per digit: its tiles' counts become their exclusive prefix
+// sums, total[digit] their sum.
+__global__ __launch_bounds__(256) void k_rs_scan(uint32_t *__restrict__ hist, int ntiles,
+                                                 uint32_t *__restrict__ total) {
+    const int lane = threadIdx.x & (kWave - 1);
+    const int bin = blockIdx.x * (256 / kWave) + threadIdx.x / kWave;
+    uint32_t *row = hist + (int64_t)bin * ntiles;
+    uint32_t carry = 0u;
+    for (int t0 = 0; t0 < ntiles; t0 += 4 * kWave) {
+        uint32_t v[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int t = t0 + k * kWave + lane;
+            v[k] = t < ntiles ? row[t] : 0u;
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int t = t0 + k * kWave + lane;
+            const uint32_t inc = wave_scan_u32(v[k], lane);
+            if (t < ntiles) row[t] = carry + inc - v[k];
+            carry += __shfl(inc, kWave - 1);
+        }
+    }
+    if (lane == 0) total[bin] = carry;
+}
+
+// A wavefront ranks its 64 * kRsItems consecutive keys by itself, counting the
+// digits in its own row of LDS; one barrier then joins the rows.
 __global__ __launch_bounds__(kRsThreads) void k_rs_scatter(
     const unsigned long long *__restrict__ kin, const uint32_t *__restrict__ vin,
     unsigned long long *__restrict__ kout, uint32_t *__restrict__ vout, int64_t n, int shift,
-    const uint32_t *__restrict__ offs, int ntiles) {
-    __shared__ uint32_t run[256];
-    __shared__ uint32_t wc[kRsThreads / kWave][256];
+    const uint32_t *__restrict__ offs, const uint32_t *__restrict__ total, int ntiles) {
+    __shared__ uint32_t wc[kRsWaves][kRsBins];
+    __shared__ uint32_t wsum[kRsWaves];
     const int tid = threadIdx.x;
     const int lane = tid & (kWave - 1);
     const int wv = tid / kWave;
     const unsigned long long lt = (1ull << lane) - 1ull;
-    run[tid] = offs[(int64_t)tid * ntiles + blockIdx.x];
-    const int64_t base = (int64_t)blockIdx.x * kRsTile;
-    for (int r = 0; r < kRsItems; ++r) {
+    const int64_t first = ((int64_t)blockIdx.x * kRsWaves + wv) * kWave * kRsItems + lane;
+    const uint32_t tot = total[tid];
+    const uint32_t off = offs[(int64_t)tid * ntiles + blockIdx.x];
+    unsigned long long key[kRsItems];
+    uint32_t val[kRsItems], pos[kRsItems];
 #pragma unroll
-        for (int w = 0; w < kRsThreads / kWave; ++w) wc[w][tid] = 0;
-        __syncthreads();
-        const int64_t i = base + r * kRsThreads + tid;
-        const bool valid = i < n;
-        unsigned long long key = valid ? kin[i] : 0ull;
-        uint32_t val = valid ? vin[i] : 0u;
-        const unsigned dig = (unsigned)(key >> shift) & 255u;
+    for (int r = 0; r < kRsItems; ++r) {
+        const int64_t i = first + r * kWave;
+        key[r] = i < n ? kin[i] : 0ull;
+        val[r] = i < n ? vin[i] : 0u;
+    }
+#pragma unroll
+    for (int w = 0; w < kRsWaves; ++w) wc[w][tid] = 0u;
+    const uint32_t inc = wave_scan_u32(tot, lane);
+    if (lane == kWave - 1) wsum[wv] = inc;
+    __syncthreads();
+    volatile uint32_t *cnt = wc[wv];
+#pragma unroll
+    for (int r = 0; r < kRsItems; ++r) {
+        const bool valid = first + r * kWave < n;
+        const unsigned dig = (unsigned)(key[r] >> shift) & (kRsBins - 1);
         unsigned long long peers = __ballot(valid);
 #pragma unroll
-        for (int b = 0; b < 8; ++b) {
+        for (int b = 0; b < kRsBits; ++b) {
             const bool bit = (dig >> b) & 1u;
             const unsigned long long m = __ballot(bit);
             peers &= bit ? m : ~m;
         }
-        const unsigned rank = (unsigned)__popcll(peers & lt);
-        if (valid && rank == 0) wc[wv][dig] = (uint32_t)__popcll(peers);
-        __syncthreads();
-        {
-            uint32_t c[kRsThreads / kWave];
+        const uint32_t rank = (uint32_t)__popcll(peers & lt);
+        const uint32_t before = cnt[dig];
+        pos[r] = before + rank;
+        if (valid && rank == 0u) cnt[dig] = before + (uint32_t)__popcll(peers);
+        __builtin_amdgcn_wave_barrier();
+    }
+    __syncthreads();
+    {
+        uint32_t b = off + inc - tot;
+        for (int w = 0; w < wv; ++w) b += wsum[w];
 #pragma unroll
-            for (int w = 0; w < kRsThreads / kWave; ++w) c[w] = wc[w][tid];
-            uint32_t b = run[tid];
+        for (int w = 0; w < kRsWaves; ++w) {
+            const uint32_t c = wc[w][tid];
+            wc[w][tid] = b;
+            b += c;
+        }
+    }
+    __syncthreads();
 #pragma unroll
-            for (int w = 0; w < kRsThreads / kWave; ++w) {
-                wc[w][tid] = b;
-                b += c[w];
-            }
-            run[tid] = b;
+    for (int r = 0; r < kRsItems; ++r) {
+        if (first + r * kWave < n) {
+            const uint32_t p = wc[wv][(unsigned)(key[r] >> shift) & (kRsBins - 1)] + pos[r];
+            kout[p] = key[r];
+            vout[p] = val[r];
         }
-        __syncthreads();
-        if (valid) {
-            const uint32_t pos = wc[wv][dig] + rank;
-            kout[pos] = key;
-            vout[pos] = val;
-        }
-        __syncthreads();
     }
 }
 
@@ -537,7 +607,7 @@ static inline unsigned blocks_for(int64_t n, int t) { return (unsigned)((n + t -
 // Builds the forest over the normalized points P (caller order); the cloud
 // ranges are ctx->offsets (host) / ctx->d_offsets (device, already copied).
 // Morton keys of the n caller-order points P (cloud index above the 45
-// Morton bits when nclouds > 1) and a stable LSD sort, 8 bits per pass: on
+// Morton bits when nclouds > 1) and a stable LSD sort, 9 bits per pass: on
 // return ka holds the sorted keys and va the caller index of each.  An odd
 // pass count leaves the result in the second buffer pair, which then becomes
 // the first.  Uses ctx->hist and ctx->scan_tmp (sized here for n).
@@ -545,8 +615,8 @@ hipError_t morton_sort(wnnc_ctx_s *ctx, const float *P, int64_t n, int nclouds, 
                        DevBuf<unsigned long long> &ka, DevBuf<unsigned long long> &kb,
                        DevBuf<uint32_t> &va, DevBuf<uint32_t> &vb) {
     hipStream_t st = ctx->stream;
-    const int ntiles = (int)((n + kRsTile - 1) / kRsTile);
-    const int64_t hsize = (int64_t)256 * ntiles;
+    const int ntiles = rs_tiles(n);
+    const int64_t hsize = (int64_t)kRsBins * (ntiles + 1);  // the digits' totals after the counts
     TRY(ka.ensure(n));
     TRY(kb.ensure(n));
     TRY(va.ensure(n));
@@ -558,12 +628,14 @@ hipError_t morton_sort(wnnc_ctx_s *ctx, const float *P, int64_t n, int nclouds, 
     unsigned long long *kin = ka.p, *kout = kb.p;
     uint32_t *vin = va.p, *vout = vb.p;
     for (int pass = 0; pass < passes; ++pass) {
-        const int shift = 8 * pass;
-        hipLaunchKernelGGL(k_rs_hist, dim3(ntiles), dim3(kRsThreads), 0, st, kin, n, shift,
-                           ctx->hist.p, ntiles);
-        TRY(exclusive_scan_u32(ctx->hist.p, ctx->hist.p, hsize, ctx->scan_tmp.p, st));
+        const int shift = kRsBits * pass;
+        uint32_t *hist = ctx->hist.p, *total = hist + (int64_t)kRsBins * ntiles;
+        hipLaunchKernelGGL(k_rs_hist, dim3(ntiles), dim3(kRsThreads), 0, st, kin, n, shift, hist,
+                           ntiles);
+        hipLaunchKernelGGL(k_rs_scan, dim3(kRsBins * kWave / 256), dim3(256), 0, st, hist, ntiles,
+                           total);
         hipLaunchKernelGGL(k_rs_scatter, dim3(ntiles), dim3(kRsThreads), 0, st, kin, vin, kout,
-                           vout, n, shift, ctx->hist.p, ntiles);
+                           vout, n, shift, hist, total, ntiles);
         unsigned long long *tk = kin;
         kin = kout;
         kout = tk;
@@ -584,11 +656,11 @@ hipError_t build_tree(wnnc_ctx_s *ctx, const float *P) {
     const int nclouds = ctx->nclouds;
     hipStream_t st = ctx->stream;
     const int64_t nchunks = (n + kChunk - 1) / kChunk;
-    const int ntiles = (int)((n + kRsTile - 1) / kRsTile);
-    const int64_t hsize = (int64_t)256 * ntiles;
+    const int ntiles = rs_tiles(n);
+    const int64_t hsize = (int64_t)kRsBins * (ntiles + 1);  // the digits' totals after the counts
     int cloud_bits = 0;
     while ((1ll << cloud_bits) < nclouds) ++cloud_bits;
-    const int passes = (kMortonBits + cloud_bits + 7) / 8;
+    const int passes = rs_passes(kMortonBits + cloud_bits);
 
     TRY(ctx->pts.ensure(n));
     TRY(ctx->perm.ensure(n));
@@ -1086,7 +1158,7 @@ hipError_t make_tasks(wnnc_ctx_s *ctx, int tpl, int split) {
 }
 
 hipError_t sort_queries(wnnc_ctx_s *ctx, const float *Q, int64_t M) {
-    TRY(morton_sort(ctx, Q, M, 1, (kMortonBits + 7) / 8, ctx->qkeys_a, ctx->qkeys_b, ctx->qperm,
+    TRY(morton_sort(ctx, Q, M, 1, rs_passes(kMortonBits), ctx->qkeys_a, ctx->qkeys_b, ctx->qperm,
                     ctx->qvals_b));
     TRY(ctx->qpts.ensure(M));
     hipLaunchKernelGGL(k_gather_points, dim3(blocks_for(M, 256)), dim3(256), 0, ctx->stream, Q,
