@@ -18,7 +18,7 @@
 // vector instructions per wavefront and 836 us on a 164k-point sphere (VALU
 // 89 % busy), 945 us on a 100k-point knot; keys and FP64 minima took that to
 // 475 and 711 us, bound by the scalar unit and its loads, and nodes tested one
-// per lane to 245 and 280 us.
+// per lane to 269 and 265 us.
 // Requires points inside [-1,1]^3 (normalized clouds).
 #include <float.h>
 
