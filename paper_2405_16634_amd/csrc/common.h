@@ -145,7 +145,7 @@ struct wnnc_ctx_s {
     DevBuf<int4> knn_groups;       // neighbour-search groups (first, last; root, end)
     int knn_ngroups = 0;           // 0: not built for the current tree
     DevBuf<unsigned long long> knn_depths;  // runs per depth, in pairs of 32-bit counts
-    DevBuf<uint32_t> knn_tmp;      // 4 n: group construction
+    DevBuf<uint32_t> knn_tmp;      // 5 n + 1: group construction
     DevBuf<int32_t> knn_idx;       // n * 16 sorted neighbour positions
     DevBuf<float> knn_d2;          // n * 16 squared distances
     DevBuf<float> feat;            // n * 48 features (caller order)
