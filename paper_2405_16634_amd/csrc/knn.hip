@@ -38,9 +38,11 @@ constexpr int kKnnStack = 512;
 // index.  Distances are not negative, so the keys, read as doubles (finite
 // ones: the upper half is a float's bits), order by distance and then index,
 // and a list is kept with FP64 minima and maxima, which issue at the FP32
-// rate.  The empty entry (FLT_MAX, index -1) is above every other.
+// rate.  The empty entry (FLT_MAX, index -1) is above every other; a NaN
+// distance (of either sign) counts as an infinite one and is above it, so
+// neither is ever taken.
 __device__ inline double cand_key(float d, int j) {
-    return __hiloint2double(__float_as_int(d), j);
+    return __hiloint2double(__float_as_int(fminf(d, __builtin_huge_valf())), j);
 }
 __device__ inline float cand_d(double k) { return __int_as_float(__double2hiint(k)); }
 __device__ inline int cand_j(double k) { return __double2loint(k); }
@@ -223,6 +225,11 @@ __global__ __launch_bounds__(kWave) void k_knn(const float4 *__restrict__ pts,
                                 fmaxf(q.z - ghz, glz - uz));
         const bool near = on && d2 <= reach;
         const bool leaf = (tp.w & kRecLeaf) != 0;
+        // the points known to lie in the cell: points outside the tree's cube
+        // and non-finite ones are in the cells along its faces
+        const bool inner = fminf(fminf(q.x, q.y), q.z) > -1.0f &&
+                           fmaxf(fmaxf(ux, uy), uz) < 1.0f;
+        const int npts = inner ? tp.z - tp.y : 0;
         uint64_t offers = __ballot(near && leaf);
 #pragma unroll 1
         while (offers) {
@@ -262,7 +269,7 @@ __global__ __launch_bounds__(kWave) void k_knn(const float4 *__restrict__ pts,
             if (__ballot(d <= bound) == 0ull) open &= ~(1ull << s);
             // the farthest corner: -min is the larger of the two extents
             const float f = box_d2(-fminf(lx, hx), -fminf(ly, hy), -fminf(lz, hz));
-            const int np = __builtin_amdgcn_readlane(tp.z - tp.y, s);
+            const int np = __builtin_amdgcn_readlane(npts, s);
             bound = np > kK ? fminf(bound, f) : bound;
         }
         reach = wave_extreme<true>(bound);
