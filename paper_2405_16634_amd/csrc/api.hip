@@ -139,7 +139,8 @@ TravArgs trav_args(wnnc_ctx_s *c, float w) {
     a.task_slot = c->task_slot.p;
     a.chain = c->task_chain.p;
     a.roots = c->d_roots.p;
-    a.parts = c->parts.p;
+    a.parts = (float *)c->parts.p;
+    a.parts64 = c->parts_wide ? c->parts.p : nullptr;
     a.ntasks = c->ntasks;
     a.nslots = c->ngroups;
     a.tpl = c->tpl;
@@ -1024,7 +1025,7 @@ static wnnc_status run_iterations(wnnc_ctx ctx, int iters, float w1, float w2, i
     // pass that reads a walk's output also runs that walk's combining pass
     // (one launch fewer); the G walk's is run by the next iteration's first
     // moment pass.
-    const bool fuse_ok = ctx->gtab_ok && !(ctx->flags & WNNC_FLAG_SEPARATE_COMBINE);
+    const bool fuse_ok = comb_in_moments(ctx) && !(ctx->flags & WNNC_FLAG_SEPARATE_COMBINE);
     TravArgs pend_g;
     bool have_pend = false;
     for (int i = start; i <= stop; ++i) {

@@ -109,7 +109,8 @@ struct wnnc_ctx_s {
     DevBuf<int32_t> split_slot;    // nsplit: group slot
     DevBuf<int2> gtab;             // ngroups: part range of each group (when gtab_ok)
     bool gtab_ok = false;          // groups are the 64-point blocks: a moment pass can combine
-    DevBuf<float> parts;           // nparts * 3 * 64
+    bool parts_wide = false;       // the parts' sums are kept in FP64 (else FP32)
+    DevBuf<double> parts;          // nparts * 3 * 64 values
     DevBuf<int4> groups;           // ngroups: first, last target; root, end node
     DevBuf<int32_t> plan;          // kPlanStride per 64-target group (plan_ok)
     bool plan_ok = false;          // the plan is the current tree's

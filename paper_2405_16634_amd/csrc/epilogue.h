@@ -104,25 +104,25 @@ __device__ inline void finish_group(const TravArgs &a, int sl, int first, int la
     }
 }
 
-// The sums of one 64-target group walked in parts [pf, pe): the parts' FP32
-// sums (component-major, 3 x 64 floats per part) added in part order in
-// FP64, BATCH parts' loads in flight before their additions (a part is within
-// 2^-24 of the sum of its terms' magnitudes).  Groups of many parts (small
-// clouds) take batches of kBatchMany, which shortens the chain of loads: 66
-// instead of 84 us of moment passes per iteration at 2k points; groups of few
-// parts take kBatchFew in the moment pass, whose occupancy the registers of a
-// large batch halve (110 instead of 120 us per iteration at 500k points).
+// The sums of one 64-target group walked in parts [pf, pe): the parts' sums
+// (component-major, 3 x 64 values of type T per part; an FP32 part is within
+// 2^-24 of the sum of its terms' magnitudes) added in part order in FP64,
+// BATCH parts' loads in flight before their additions.  Groups of many parts
+// (more than two batches of kBatchFew on average) take batches of kBatchMany,
+// which shortens the chain of loads; groups of few parts take kBatchFew in the
+// moment pass, whose occupancy the registers of a large batch halve (110
+// instead of 120 us of moment passes per iteration at 500k points).
 constexpr int kBatchFew = 4, kBatchMany = 16;
 
-template <int OP, int BATCH>
-__device__ inline void sum_parts(const float *parts, int pf, int pe, int lane, double &s,
-                                 double &gx, double &gy, double &gz) {
+template <int OP, int BATCH, class T>
+__device__ inline void sum_parts(const T *parts, int pf, int pe, int lane, double &s, double &gx,
+                                 double &gy, double &gz) {
     for (int p0 = pf; p0 < pe; p0 += BATCH) {
-        float v0[BATCH], v1[BATCH], v2[BATCH];
+        T v0[BATCH], v1[BATCH], v2[BATCH];
 #pragma unroll
         for (int u = 0; u < BATCH; ++u) {
             // (a part past the group's last reads the last one; not added)
-            const float *qp = parts + (int64_t)min(p0 + u, pe - 1) * (3 * kWave);
+            const T *qp = parts + (int64_t)min(p0 + u, pe - 1) * (3 * kWave);
             v0[u] = qp[lane];
             if (OP != OP_A) {
                 v1[u] = qp[kWave + lane];

@@ -194,7 +194,8 @@ struct TravArgs {
     const int32_t *task_slot;  // >= 0: group slot (whole walk); < 0: -1 - part slot
     const int32_t *chain;    // per task: ancestors of its first node (kChainStride ints)
     const int32_t *roots;    // first node of each cloud (nclouds + 1)
-    float *parts;            // per part slot: 3 x 64 sums rounded to FP32 (component-major)
+    float *parts;            // per part slot: 3 x 64 sums rounded to FP32 (component-major),
+    double *parts64;         // or, where not null, in FP64 here instead
     int ntasks;              // wavefronts launched
     int nslots;              // groups: row stride of the per-group partial sums
     int tpl;                 // target groups of 64 per wavefront (1, 2, 4)

@@ -178,7 +178,7 @@ struct CombOf {
 
 // One chunk (the workgroup's): for the MOM_COMB_* modes ta is the walk's
 // arguments, else null.
-template <int MODE, bool HI, int BATCH = kBatchFew>
+template <int MODE, bool HI, int BATCH = kBatchFew, class T = float>
 __device__ __forceinline__ void chunk_body(const MomArgs &a, const TravArgs *ta) {
     constexpr bool COMB = MODE >= MOM_COMB_RHO;
     constexpr int kMomVals = mom_vals<HI>();
@@ -221,7 +221,10 @@ __device__ __forceinline__ void chunk_body(const MomArgs &a, const TravArgs *ta)
             if (pr.y > pr.x) {
                 constexpr int OP = CombOf<MODE>::op, TM = CombOf<MODE>::mode;
                 double s = 0.0, gx = 0.0, gy = 0.0, gz = 0.0;
-                sum_parts<OP, BATCH>(ta->parts, pr.x, pr.y, lane, s, gx, gy, gz);
+                const T *parts;
+                if constexpr (sizeof(T) == sizeof(double)) parts = ta->parts64;
+                else parts = ta->parts;
+                sum_parts<OP, BATCH>(parts, pr.x, pr.y, lane, s, gx, gy, gz);
                 double e = 0.0, e2 = 0.0;
                 unsigned nflip = 0;
                 if (i < a.n) finish_target<OP, TM>(*ta, i, s, gx, gy, gz, e, e2, nflip, cnu);
@@ -348,9 +351,9 @@ __global__ __launch_bounds__(kChunk) void k_moments_chunk(MomArgs a) {
 
 // The chunk pass that also runs the combining pass of the walk launched
 // before it (MOM_COMB_*; without the far field).
-template <int MODE, int BATCH>
+template <int MODE, int BATCH, class T>
 __global__ __launch_bounds__(kChunk) void k_moments_comb(MomArgs a, TravArgs ta) {
-    chunk_body<MODE, false, BATCH>(a, &ta);
+    chunk_body<MODE, false, BATCH, T>(a, &ta);
 }
 
 // Straddlers: head + totals of the chunks in between + tail.  A straddler
@@ -470,31 +473,37 @@ hipError_t launch_moments_t(wnnc_ctx_s *ctx, MomMode mode, const MomArgs &a) {
     return launch_strad<HI>(ctx, a);
 }
 
+template <int MODE>
+static hipError_t launch_comb_t(wnnc_ctx_s *ctx, bool many, bool wide, bool last, dim3 grid,
+                                const MomArgs &a, const TravArgs &ta) {
+    void (*k)(MomArgs, TravArgs) = wide   ? k_moments_comb<MODE, kBatchFew, double>
+                                   : many ? k_moments_comb<MODE, kBatchMany, float>
+                                          : k_moments_comb<MODE, kBatchFew, float>;
+    return launch_k(ctx->lev, last, k, grid, dim3(kChunk), ctx->stream, a, ta);
+}
+
+static bool many_parts(const wnnc_ctx_s *ctx) {
+    return ctx->nparts > 2 * kBatchFew * ctx->nsplit;
+}
+
+bool comb_in_moments(const wnnc_ctx_s *ctx) {
+    return ctx->gtab_ok && !(ctx->parts_wide && many_parts(ctx));
+}
+
 hipError_t launch_moments_comb(wnnc_ctx_s *ctx, MomMode mode, const MomArgs &args,
                                const TravArgs &ta) {
     MomArgs a = args;
     a.scalar = mode == MOM_COMB_RHO;
     if (a.order > 0 || !a.gtab || ta.tpl != 1) return hipErrorInvalidValue;
-    const dim3 grid((unsigned)((a.n + kChunk - 1) / kChunk)), block(kChunk);
+    const dim3 grid((unsigned)((a.n + kChunk - 1) / kChunk));
     const bool last = a.n_strad <= 0;
     hipError_t e = hipErrorInvalidValue;
-    // (more than two batches of kBatchFew parts per group on average)
-    const bool many = ctx->nparts > 2 * kBatchFew * ctx->nsplit;
-    auto launch = [&](void (*few_k)(MomArgs, TravArgs), void (*many_k)(MomArgs, TravArgs)) {
-        return launch_k(ctx->lev, last, many ? many_k : few_k, grid, block, ctx->stream, a, ta);
-    };
+    const bool many = many_parts(ctx), wide = ta.parts64 != nullptr;
     switch (mode) {
-        case MOM_COMB_RHO:
-            e = launch(k_moments_comb<MOM_COMB_RHO, kBatchFew>,
-                       k_moments_comb<MOM_COMB_RHO, kBatchMany>);
-            break;
-        case MOM_COMB_R:
-            e = launch(k_moments_comb<MOM_COMB_R, kBatchFew>,
-                       k_moments_comb<MOM_COMB_R, kBatchMany>);
-            break;
+        case MOM_COMB_RHO: e = launch_comb_t<MOM_COMB_RHO>(ctx, many, wide, last, grid, a, ta); break;
+        case MOM_COMB_R: e = launch_comb_t<MOM_COMB_R>(ctx, many, wide, last, grid, a, ta); break;
         case MOM_COMB_RESCALE:
-            e = launch(k_moments_comb<MOM_COMB_RESCALE, kBatchFew>,
-                       k_moments_comb<MOM_COMB_RESCALE, kBatchMany>);
+            e = launch_comb_t<MOM_COMB_RESCALE>(ctx, many, wide, last, grid, a, ta);
             break;
         default:
             break;

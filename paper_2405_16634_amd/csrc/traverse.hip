@@ -722,8 +722,20 @@ __global__ __launch_bounds__(kTravBlock) void k_traverse(TravArgs a) {
     if (COUNT) {  // cnt is wave-uniform: the pairs of all lanes
         if (lane == 0) atomicAdd(a.pairs + OP, (unsigned long long)cnt);
     }
-    if (tslot < 0) {  // one part of a split walk (TPL = 1): its sums, rounded to FP32
-        float *qp = a.parts + (int64_t)(-1 - tslot) * (3 * kWave);
+    if (tslot < 0) {  // one part of a split walk (TPL = 1): its sums
+        const int64_t at = (int64_t)(-1 - tslot) * (3 * kWave);
+        if (a.parts64) {
+            double *qp = a.parts64 + at;
+            if (OP == OP_A) {
+                qp[lane] = s[0];
+            } else {
+                qp[lane] = gx[0];
+                qp[kWave + lane] = gy[0];
+                qp[2 * kWave + lane] = gz[0];
+            }
+            return;
+        }
+        float *qp = a.parts + at;
         if (OP == OP_A) {
             qp[lane] = (float)s[0];
         } else {
@@ -752,7 +764,10 @@ __global__ __launch_bounds__(kWave) void k_combine(TravArgs a, const int4 *__res
     const int lane = threadIdx.x;
     const int4 g = ldc_i4(groups + blockIdx.x);
     double s = 0.0, gx = 0.0, gy = 0.0, gz = 0.0;
-    sum_parts<OP, kBatchMany>(a.parts, g.z, g.w, lane, s, gx, gy, gz);
+    if (a.parts64)
+        sum_parts<OP, kBatchMany>(a.parts64, g.z, g.w, lane, s, gx, gy, gz);
+    else
+        sum_parts<OP, kBatchMany>(a.parts, g.z, g.w, lane, s, gx, gy, gz);
     double e = 0.0, e2 = 0.0;
     unsigned nflip = 0;
     const int t = g.x + lane;

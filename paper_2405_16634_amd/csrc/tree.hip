@@ -1109,7 +1109,10 @@ constexpr unsigned long long kFillParts = 16384;
 // Parts of the split size itself are cut at every kCoarseStep-th node of the
 // plan (64 visits): finer cuts balance them no better than 2 % (332 instead of
 // 338 us at 500k points), and these keep the grouping, and so the bits, of the
-// sums of large clouds independent of the plan's resolution.
+// sums of large clouds independent of the plan's resolution.  Their sums are
+// rounded to FP32, once per 64 visits or more.  Shorter parts keep FP64 sums:
+// they also split walks that would otherwise be whole, whose sums meet FP32
+// only in the output.
 constexpr int kCoarseStep = 4;
 
 // Wavefront tasks for tile shape tpl: each cloud's sorted targets cut into
@@ -1160,6 +1163,7 @@ hipError_t make_tasks(wnnc_ctx_s *ctx, int tpl, int split) {
             std::max<unsigned long long>(ctx->plan_visits / kFillParts, kPlanStep));
         if (eff == split) step = kCoarseStep;
     }
+    const bool wide = use_plan && step < kCoarseStep;
     hipLaunchKernelGGL(k_cuts, dim3(blocks_for(g, 256 / kWave)), dim3(256), 0, st, ctx->groups.p,
                        ctx->plan.p, ng, eff, step, ctx->cuts.p, ctx->ncuts.p);
     hipLaunchKernelGGL(k_part_scan, dim3(1), dim3(kPartScan), 0, st, ctx->ncuts.p, ng,
@@ -1180,7 +1184,8 @@ hipError_t make_tasks(wnnc_ctx_s *ctx, int tpl, int split) {
     TRY(ctx->task_slot.ensure(nt));
     TRY(ctx->split_groups.ensure(ns > 0 ? ns : 1));
     TRY(ctx->split_slot.ensure(ns > 0 ? ns : 1));
-    TRY(ctx->parts.ensure(np > 0 ? (int64_t)np * 3 * kWave : 1));
+    const int64_t nv = (int64_t)np * 3 * kWave;
+    TRY(ctx->parts.ensure(std::max<int64_t>(wide ? nv : nv / 2, 1)));
     TRY(ctx->task_chain.ensure(nt * kChainStride));
     hipLaunchKernelGGL(k_emit_tasks, dim3(blocks_for(g * kWave, 256)), dim3(256), 0, st,
                        ctx->groups.p, ctx->cuts.p, ctx->ncuts.p, ctx->part_off.p,
@@ -1191,6 +1196,7 @@ hipError_t make_tasks(wnnc_ctx_s *ctx, int tpl, int split) {
                        ctx->task_chain.p);
     TRY(hipGetLastError());
     ctx->gtab_ok = aligned;
+    ctx->parts_wide = wide;
     ctx->ntasks = (int)nt;
     ctx->ngroups = ng;
     ctx->nparts = (int)np;
