@@ -1195,6 +1195,8 @@ hipError_t make_tasks(wnnc_ctx_s *ctx, int tpl, int split) {
                        ctx->cloud_of.p, ctx->d_roots.p, ctx->topo.p, ctx->mom.p, (int)nt,
                        ctx->task_chain.p);
     TRY(hipGetLastError());
+    // the tasks are complete on return: the next walk may be on another stream
+    TRY(hipStreamSynchronize(st));
     ctx->gtab_ok = aligned;
     ctx->parts_wide = wide;
     ctx->ntasks = (int)nt;
