@@ -436,6 +436,15 @@ static hipError_t setup_tasks(wnnc_ctx_s *ctx, int tpl, int split) {
     return make_tasks(ctx, tpl, split);
 }
 
+// New tasks for the tree at hand.  If that fails, the old ones are partly
+// replaced: the tree counts as not built.
+static wnnc_status replace_tasks(wnnc_ctx_s *ctx, int tpl, int split) {
+    const hipError_t e = setup_tasks(ctx, tpl, split);
+    if (e == hipSuccess) return WNNC_OK;
+    ctx->built = false;
+    return fail(WNNC_EDEVICE, "tasks: %s (build the tree again)", hipGetErrorString(e));
+}
+
 static wnnc_status build_impl(wnnc_ctx ctx, const float *P, const int64_t *offsets, int B,
                               const wnnc_tree_opts *opts) {
     int64_t N = 0;
@@ -512,8 +521,7 @@ wnnc_status wnnc_set_tile(wnnc_ctx ctx, int tpl) {
     CHECK_CTX(ctx);
     if (tpl != 1 && tpl != 2 && tpl != 4) return fail(WNNC_EINVAL, "tile must be 1, 2 or 4");
     if (ctx->built) {
-        hipError_t e = setup_tasks(ctx, tpl, ctx->split);
-        if (e != hipSuccess) return fail(WNNC_EDEVICE, "tasks: %s", hipGetErrorString(e));
+        RETURN_IF(replace_tasks(ctx, tpl, ctx->split));
     } else {
         ctx->tpl = tpl;
     }
@@ -525,8 +533,7 @@ wnnc_status wnnc_set_split(wnnc_ctx ctx, int visits) {
     if (visits < 0 || visits > WNNC_MAX_SPLIT)
         return fail(WNNC_EINVAL, "split must be in 0..%d", WNNC_MAX_SPLIT);
     if (ctx->built) {
-        hipError_t e = setup_tasks(ctx, ctx->tpl, visits);
-        if (e != hipSuccess) return fail(WNNC_EDEVICE, "tasks: %s", hipGetErrorString(e));
+        RETURN_IF(replace_tasks(ctx, ctx->tpl, visits));
     } else {
         ctx->split = visits;
     }
@@ -631,8 +638,7 @@ wnnc_status wnnc_autotune(wnnc_ctx ctx, float w, wnnc_tile_time *times_out) {
     };
     double tk[WNNC_AUTOTUNE_CONFIGS];
     for (int k = 0; k < WNNC_AUTOTUNE_CONFIGS / 2; ++k) {
-        hipError_t e = setup_tasks(ctx, cand[k][0], cand[k][1]);
-        if (e != hipSuccess) return fail(WNNC_EDEVICE, "tasks: %s", hipGetErrorString(e));
+        RETURN_IF(replace_tasks(ctx, cand[k][0], cand[k][1]));
         for (int pf = 0; pf < 2; ++pf) {
             double t;
             RETURN_IF(time_setting(pf, kTuneReps, &t));
@@ -661,8 +667,7 @@ wnnc_status wnnc_autotune(wnnc_ctx ctx, float w, wnnc_tile_time *times_out) {
         if (near.size() > 1) {
             for (int round = 0; round < kRetimeRounds; ++round) {
                 for (int c : near) {
-                    hipError_t e = setup_tasks(ctx, cand[c / 2][0], cand[c / 2][1]);
-                    if (e != hipSuccess) return fail(WNNC_EDEVICE, "tasks: %s", hipGetErrorString(e));
+                    RETURN_IF(replace_tasks(ctx, cand[c / 2][0], cand[c / 2][1]));
                     double t;
                     RETURN_IF(time_setting(c % 2, 1, &t));
                     tk[c] = std::min(tk[c], t);
@@ -683,8 +688,7 @@ wnnc_status wnnc_autotune(wnnc_ctx ctx, float w, wnnc_tile_time *times_out) {
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     ctx->prefetch = best_pf;
-    hipError_t e = setup_tasks(ctx, best, best_split);
-    if (e != hipSuccess) return fail(WNNC_EDEVICE, "tasks: %s", hipGetErrorString(e));
+    RETURN_IF(replace_tasks(ctx, best, best_split));
     // Then the walk per operator on the chosen tiles: the same iterations
     // with each operator's traversal launches timed (the events ride on the
     // launches), without and with prefetch; an operator takes the other

@@ -1123,6 +1123,9 @@ bool needs_plan(const wnnc_ctx_s *ctx, int tpl, int split) {
 
 hipError_t make_tasks(wnnc_ctx_s *ctx, int tpl, int split) {
     hipStream_t st = ctx->stream;
+    // (no tasks until all of them are there)
+    ctx->gtab_ok = false;
+    ctx->ntasks = ctx->nparts = ctx->nsplit = ctx->ngroups = 0;
     const int per = kWave * tpl;
     std::vector<int32_t> lo(ctx->nclouds + 1);
     int64_t g = 0;

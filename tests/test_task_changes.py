@@ -67,3 +67,34 @@ for change, v in ((lib.wnnc_set_split, 64), (lib.wnnc_set_split, 0), (lib.wnnc_s
     assert host.host_pending() == 0, (v, host.host_pending())
 lib.wnnc_destroy(h)
 """)
+
+
+def test_a_failed_change_leaves_no_tasks_to_launch(run):
+    """Every allocation that a change of tasks makes fails once: the call
+    reports it, and the next operator is refused instead of launched on
+    half-replaced tables; after another build everything works."""
+    out = run("""
+adjoint = lambda h: lib.wnnc_adjoint(h, ctypes.addressof(s), 0.002, ctypes.addressof(out))
+failed = 0
+for k in range(1, 40):
+    h = context(4)
+    host.host_fail_allocation(k)
+    status = lib.wnnc_set_tile(h, 1)
+    assert status == 0 or b"out of memory" in lib.wnnc_last_error()
+    host.host_fail_allocation(0)
+    before = host.host_launches()
+    ran = adjoint(h)
+    launched = host.host_launches() - before
+    if status == 0:
+        assert ran == 0 and launched > 0
+        break
+    failed += 1
+    assert ran != 0 and launched == 0, (k, ran, launched)
+    assert lib.wnnc_build(h, P, N, None) == 0, lib.wnnc_last_error()
+    assert adjoint(h) == 0
+    lib.wnnc_destroy(h)
+else:
+    raise AssertionError("the change never succeeded")
+print("failed", failed)
+""")
+    assert int(out.split("failed")[1]) >= 8
