@@ -322,6 +322,7 @@ wnnc_status wnnc_destroy(wnnc_ctx ctx) {
     ctx->groups.release();
     ctx->plan.release();
     ctx->plan_sum.release();
+    ctx->plan_longs.release();
     ctx->cuts.release();
     ctx->ncuts.release();
     ctx->part_off.release();

@@ -115,7 +115,8 @@ struct wnnc_ctx_s {
     DevBuf<int32_t> plan;          // kPlanStride per 64-target group (plan_ok)
     bool plan_ok = false;          // the plan is the current tree's
     unsigned long long plan_visits = 0;  // visits of all walks in the plan
-    DevBuf<unsigned long long> plan_sum;
+    DevBuf<unsigned long long> plan_sum;  // the visits; groups of more than kPlanVisits
+    DevBuf<int32_t> plan_longs;    // those groups
     DevBuf<int32_t> cuts;          // ngroups * kPlanStride: first nodes of the parts after the first
     DevBuf<uint32_t> ncuts;        // ngroups: parts of a split walk (0: whole)
     DevBuf<uint32_t> part_off, split_off;  // ngroups + 1: parts and split groups before each group

@@ -124,10 +124,11 @@ enum TravMode {
     TR_ACCUM = 8,       // out = sum / (4 pi) + base, caller order (base in gradf)
 };
 
-// Split planning: the nodes that the walk of a 64-target group visits (as its
-// bounding box sees them, at most kPlanVisits) are listed in walk order, and
-// the plan holds their number and every kPlanStep-th of them, kPlanStride ints
-// per group.
+// Split planning: the nodes that the walk of a 64-target group visits (those
+// with the root or an opened node as parent, every target tested) are put in
+// walk order, and the plan holds their number and every kPlanStep-th of them,
+// kPlanStride ints per group; of more than kPlanVisits, every 2nd, 4th, ... of
+// those.
 constexpr int kPlanStep = 16;
 constexpr int kPlanVisits = 4096;
 constexpr int kPlanStride = kPlanVisits / kPlanStep;

@@ -836,12 +836,9 @@ __global__ __launch_bounds__(256) void k_groups(const int32_t *__restrict__ lo,
 // against Alg. 4's threshold, the boxes of kPlanPer targets first), and sorts
 // them by index, which is the order of the walk.  Bound by the rounds of loads
 // and LDS accesses, about a dozen, where a recording walk is a chain of up to
-// 2,600 visits: the build takes 1.25 instead of 1.67 ms at 500k points and
-// 0.54 instead of 0.60 ms at 2k (half of the gain is the tasks made here
-// instead of on the host).  The list has to be exact: with the box of all 64
-// targets instead of the targets the A walk takes 132 instead of 74 us at
-// 100k points, and with cell centres for x_B 341 instead of 332 us at 500k.
-// A list that overflows (a huge c) is replaced by nodes at equal spacing.
+// 2,600 visits.  The list has to be exact: with the box of all 64 targets
+// instead of the targets the A walk takes 132 instead of 74 us at 100k points,
+// and with cell centres for x_B 341 instead of 332 us at 500k.
 // The boxes are tested without a branch between them, and the sort shifts
 // instead of dividing and meets a barrier only where pairs span wavefronts:
 // 118 -> 80 us at 50k points, 207 -> 142 us at 164k.  The loops are unrolled
@@ -850,42 +847,93 @@ __global__ __launch_bounds__(256) void k_groups(const int32_t *__restrict__ lo,
 constexpr int kPlanBlock = 256;
 constexpr int kPlanPer = 8, kPlanBoxes = kWave / kPlanPer;
 
-__global__ __launch_bounds__(kPlanBlock) void k_plan(const int4 *__restrict__ groups,
-                                                     const float4 *__restrict__ tpts,
-                                                     const float4 *__restrict__ cells,
-                                                     const float4 *__restrict__ mom,
-                                                     const int4 *__restrict__ topo, float c,
-                                                     int32_t *__restrict__ plan,
-                                                     unsigned long long *__restrict__ sum) {
-    __shared__ int vis[kPlanVisits];
-    __shared__ float4 box[kPlanBoxes][2];  // lower corner, negated upper corner
-    __shared__ float4 tgt[kWave];
-    __shared__ int tail;
-    const int tid = threadIdx.x, lane = tid & (kWave - 1);
-    const int4 G = groups[blockIdx.x];
-    if (tid < kWave) {
-        // the group's last target in place of those it lacks
-        const float4 p = tpts[min(G.x + lane, G.y - 1)];
-        float v[6] = {p.x, p.y, p.z, -p.x, -p.y, -p.z};
-        tgt[lane] = p;
+// A group's targets as a plan tests them (in LDS).
+struct PlanTargets {
+    float4 box[kPlanBoxes][2];  // lower corner, negated upper corner
+    float4 tgt[kWave];
+};
+
+// Filled by the workgroup's first wavefront.
+__device__ inline void plan_targets(PlanTargets &T, const int4 &G,
+                                    const float4 *__restrict__ tpts, int lane) {
+    // the group's last target in place of those it lacks
+    const float4 p = tpts[min(G.x + lane, G.y - 1)];
+    float v[6] = {p.x, p.y, p.z, -p.x, -p.y, -p.z};
+    T.tgt[lane] = p;
 #pragma unroll
-        for (int k = 0; k < 6; ++k)
+    for (int k = 0; k < 6; ++k)
 #pragma unroll
-            for (int d = 1; d < kPlanPer; d <<= 1) v[k] = fminf(v[k], __shfl_xor(v[k], d, kWave));
-        if (lane % kPlanPer == 0) {
-            box[lane / kPlanPer][0] = make_float4(v[0], v[1], v[2], 0.0f);
-            box[lane / kPlanPer][1] = make_float4(v[3], v[4], v[5], 0.0f);
+        for (int d = 1; d < kPlanPer; d <<= 1) v[k] = fminf(v[k], __shfl_xor(v[k], d, kWave));
+    if (lane % kPlanPer == 0) {
+        T.box[lane / kPlanPer][0] = make_float4(v[0], v[1], v[2], 0.0f);
+        T.box[lane / kPlanPer][1] = make_float4(v[3], v[4], v[5], 0.0f);
+    }
+}
+
+// Whether some target does not accept the node at (x, y, z).
+__device__ inline bool plan_opens(const PlanTargets &T, float x, float y, float z, float thr2) {
+    unsigned near = 0u;
+#pragma unroll 2
+    for (int b = 0; b < kPlanBoxes; ++b) {
+        const float4 bl = T.box[b][0], bh = T.box[b][1];
+        const float dx = fmaxf(fmaxf(bl.x - x, x + bh.x), 0.f),
+                    dy = fmaxf(fmaxf(bl.y - y, y + bh.y), 0.f),
+                    dz = fmaxf(fmaxf(bl.z - z, z + bh.z), 0.f);
+        near |= fmaf(dx, dx, fmaf(dy, dy, dz * dz)) > thr2 ? 0u : 1u << b;
+    }
+    bool open = false;
+    while (near != 0u && !open) {
+        const float4 *tb = T.tgt + kPlanPer * __builtin_ctz(near);
+        near &= near - 1u;
+#pragma unroll 4
+        for (int t = 0; t < kPlanPer; ++t) {
+            const float ex = tb[t].x - x, ey = tb[t].y - y, ez = tb[t].z - z;
+            open |= fmaf(ex, ex, fmaf(ey, ey, ez * ez)) <= thr2;
         }
     }
+    return open;
+}
+
+// The children of node nd (record words fl and R3), in order: see(q, kid).
+template <class See>
+__device__ inline void plan_kids(int nd, int fl, const float4 &R3, const int4 *__restrict__ topo,
+                                 See &&see) {
+    const int nk = fl >> kRecKidShift;
+    const uint32_t w[4] = {__float_as_uint(R3.x), __float_as_uint(R3.y), __float_as_uint(R3.z),
+                           __float_as_uint(R3.w)};
+    int kid = nd + 1;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+        if (q < nk) {
+            if (q > 0)
+                kid = (fl & kRecWideKids)
+                          ? topo[kid].x
+                          : nd + (int)((w[(q - 1) / 2] >> (16 * ((q - 1) & 1))) & 0xffffu);
+            see(q, kid);
+        }
+    }
+}
+
+// Lists the nodes that the walk from `root` visits, a level per round: level
+// by level until all are listed (returns -1; tail is their number) or a level
+// does not fit into vis (returns the depth of the last level that did; *listed
+// is the number of nodes down to it).  All threads of the workgroup call it.
+__device__ inline int plan_list(const PlanTargets &T, int root, int *vis, int &tail,
+                                const float4 *__restrict__ cells, const float4 *__restrict__ mom,
+                                const int4 *__restrict__ topo, float c, int tid, int *listed) {
     if (tid == 0) {
-        vis[0] = G.z;
+        vis[0] = root;
         tail = 1;
     }
     int head = 0;
-    for (;;) {
+    for (int level = 0;; ++level) {
         __syncthreads();
-        const int end = min(tail, kPlanVisits);
+        const int end = tail;
         __syncthreads();
+        if (end > kPlanVisits) {
+            *listed = head;
+            return level - 1;
+        }
         if (head >= end) break;
         for (int i = head + tid; i < end; i += kPlanBlock) {
             const int nd = vis[i];
@@ -893,57 +941,23 @@ __global__ __launch_bounds__(kPlanBlock) void k_plan(const int4 *__restrict__ gr
             const float4 cb = cells[nd], R0 = rb[0], R3 = rb[3];
             if (cb.w < 0.0f) continue;  // a single-point leaf
             const int fl = __float_as_int(R0.w);
-            const float x = R0.x, y = R0.y, z = R0.z;
             const float thr2 = (c * cb.w) * (c * cb.w);
-            unsigned near = 0u;
-#pragma unroll 2
-            for (int b = 0; b < kPlanBoxes; ++b) {
-                const float4 bl = box[b][0], bh = box[b][1];
-                const float dx = fmaxf(fmaxf(bl.x - x, x + bh.x), 0.f),
-                            dy = fmaxf(fmaxf(bl.y - y, y + bh.y), 0.f),
-                            dz = fmaxf(fmaxf(bl.z - z, z + bh.z), 0.f);
-                near |= fmaf(dx, dx, fmaf(dy, dy, dz * dz)) > thr2 ? 0u : 1u << b;
-            }
-            bool open = false;
-            while (near != 0u && !open) {
-                const float4 *tb = tgt + kPlanPer * __builtin_ctz(near);
-                near &= near - 1u;
-#pragma unroll 4
-                for (int t = 0; t < kPlanPer; ++t) {
-                    const float ex = tb[t].x - x, ey = tb[t].y - y, ez = tb[t].z - z;
-                    open |= fmaf(ex, ex, fmaf(ey, ey, ez * ez)) <= thr2;
-                }
-            }
-            if (!open) continue;
+            if (!plan_opens(T, R0.x, R0.y, R0.z, thr2)) continue;
             const int nk = fl >> kRecKidShift;
             if (nk == 0) continue;  // a leaf
             const int o = atomicAdd(&tail, nk);
-            const uint32_t w[4] = {__float_as_uint(R3.x), __float_as_uint(R3.y),
-                                   __float_as_uint(R3.z), __float_as_uint(R3.w)};
-            int kid = nd + 1;
-#pragma unroll
-            for (int q = 0; q < 8; ++q) {
-                if (q < nk) {
-                    if (q > 0)
-                        kid = (fl & kRecWideKids)
-                                  ? topo[kid].x
-                                  : nd + (int)((w[(q - 1) / 2] >> (16 * ((q - 1) & 1))) & 0xffffu);
-                    if (o + q < kPlanVisits) vis[o + q] = kid;
-                }
-            }
+            plan_kids(nd, fl, R3, topo, [&](int q, int kid) {
+                if (o + q < kPlanVisits) vis[o + q] = kid;
+            });
         }
         head = end;
     }
-    const int n = min(tail, kPlanVisits);
-    int32_t *out = plan + (int64_t)blockIdx.x * kPlanStride;
-    if (tail > kPlanVisits) {
-        for (int k = tid; k < kPlanStride; k += kPlanBlock)
-            out[k] = k == 0 ? kPlanVisits
-                            : G.z + (int)((int64_t)(G.w - G.z) * k / kPlanStride);
-        if (tid == 0) atomicAdd(sum, (unsigned long long)kPlanVisits);
-        return;
-    }
-    // bitonic sort of the n entries, padded to a power of two
+    *listed = head;
+    return -1;
+}
+
+// Bitonic sort of vis[0 .. n), padded to a power of two.
+__device__ inline void plan_sort(int *vis, int n, int tid) {
     int m = 2;
     while (m < n) m <<= 1;
     for (int i = n + tid; i < m; i += kPlanBlock) vis[i] = INT32_MAX;
@@ -969,14 +983,161 @@ __global__ __launch_bounds__(kPlanBlock) void k_plan(const int4 *__restrict__ gr
         }
     }
     __syncthreads();
+}
+
+// Visits between two nodes that a plan holds: kPlanStep, doubled until a walk
+// of n visits has no more than kPlanStride of them.
+__device__ inline int plan_step(int n) {
+    int step = kPlanStep;
+    while ((int64_t)step * kPlanStride < n) step <<= 1;
+    return step;
+}
+
+// sum[0] += the planned visits; a group of more than kPlanVisits is appended
+// to `longs` instead (their number in sum[1]) and planned by k_plan_long.
+__global__ __launch_bounds__(kPlanBlock) void k_plan(const int4 *__restrict__ groups,
+                                                     const float4 *__restrict__ tpts,
+                                                     const float4 *__restrict__ cells,
+                                                     const float4 *__restrict__ mom,
+                                                     const int4 *__restrict__ topo, float c,
+                                                     int32_t *__restrict__ plan,
+                                                     unsigned long long *__restrict__ sum,
+                                                     int32_t *__restrict__ longs) {
+    __shared__ int vis[kPlanVisits];
+    __shared__ PlanTargets T;
+    __shared__ int tail;
+    const int tid = threadIdx.x;
+    const int4 G = groups[blockIdx.x];
+    if (tid < kWave) plan_targets(T, G, tpts, tid);
+    int n;
+    if (plan_list(T, G.z, vis, tail, cells, mom, topo, c, tid, &n) >= 0) {
+        if (tid == 0) longs[atomicAdd(sum + 1, 1ull)] = (int32_t)blockIdx.x;
+        return;
+    }
+    int32_t *out = plan + (int64_t)blockIdx.x * kPlanStride;
+    plan_sort(vis, n, tid);
     for (int k = tid; k * kPlanStep < n; k += kPlanBlock) out[k] = k == 0 ? n : vis[k * kPlanStep];
     if (tid == 0) atomicAdd(sum, (unsigned long long)n);
+}
+
+// Plans of more than kPlanVisits visits (on a surface of 500k points those of
+// some groups at c = 3, of nearly all at c = 5): the levels that fit are listed
+// as in k_plan, and each node of the last one stands for all visits below it,
+// which the workgroup counts with a stack of nodes in LDS, up to a node per
+// thread at a time.  The plan is the listed node nearest to every plan_step-th
+// visit.  (Finding the nodes between them as well, by a thread that walks below
+// a listed one, makes no walk faster: A 1217 and 1202 us at 500k points and
+// c = 4, the build 2750 and 2370 us.)  Bound by the rounds of the stack: loads,
+// then three barriers.  Nodes at equal spacing over the cloud in place of this
+// cut such walks very unevenly, as their visits are around their targets: the A
+// walk took 388 us on a 100k-point sphere at c = 4, now 195; cutting up to visit
+// 4,032 of a recorded walk and not beyond took 1555 us at 500k points and c = 4,
+// now 1202 (the build 3280 and 2370 us; at c = 5 4340 and 3020).
+constexpr int kPlanStack = 2048;  // a step leaves room for 8 entries per level below one node
+
+__global__ __launch_bounds__(kPlanBlock) void k_plan_long(
+    const int4 *__restrict__ groups, const float4 *__restrict__ tpts,
+    const float4 *__restrict__ cells, const float4 *__restrict__ mom,
+    const int4 *__restrict__ topo, float c, int32_t *__restrict__ plan,
+    unsigned long long *__restrict__ sum, const int32_t *__restrict__ longs) {
+    constexpr int kPer = kPlanVisits / kPlanBlock, kRoom = kPlanStack - 8 * kMaxDepth;
+    __shared__ int vis[kPlanVisits], pos[kPlanVisits];
+    __shared__ int stack[kPlanStack];
+    __shared__ uint16_t owner[kPlanStack];  // the listed node above (kPlanVisits of them)
+    __shared__ PlanTargets T;
+    __shared__ int tail, sp, wsum[kPlanBlock / kWave];
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
+    const int g = longs[blockIdx.x];
+    const int4 G = groups[g];
+    if (tid < kWave) plan_targets(T, G, tpts, tid);
+    int n;
+    const int last = plan_list(T, G.z, vis, tail, cells, mom, topo, c, tid, &n);
+    __syncthreads();
+    plan_sort(vis, n, tid);
+    // the visits of every listed node: its own, and of the last level those
+    // below it
+    for (int i = tid; i < kPlanVisits; i += kPlanBlock) pos[i] = i < n ? 1 : 0;
+    if (tid == 0) sp = 0;
+    int next = 0;  // the next listed node to look below
+    for (;;) {
+        __syncthreads();
+        // nodes from the stack, then listed ones: never more than their
+        // children fit; one at a time if need be, depth first
+        const int s = sp;
+        const int t = min(min(s, kPlanBlock), max(1, (kRoom - s) / 7));
+        const int f = min(min(kPlanBlock - t, n - next), max(0, (kRoom - s - 7 * t) / 8));
+        if (t + f == 0) break;
+        int nd = -1, own = 0;
+        if (tid < t) {
+            nd = stack[s - 1 - tid];
+            own = owner[s - 1 - tid];
+        } else if (tid < t + f) {
+            own = next + tid - t;
+            nd = vis[own];
+        }
+        __syncthreads();
+        if (tid == 0) sp = s - t;
+        __syncthreads();
+        if (nd >= 0) {
+            const float4 *rb = mom + (int64_t)kRecStride * nd;
+            const float4 R0 = rb[0], R3 = rb[3];
+            const int fl = __float_as_int(R0.w), nk = fl >> kRecKidShift;
+            const float cw = c * ldexpf(1.0f, 1 - (fl & 15));
+            // (the children of a listed node above the last level are listed)
+            if (nk > 0 && (fl & 15) >= last && plan_opens(T, R0.x, R0.y, R0.z, cw * cw)) {
+                atomicAdd(&pos[own], nk);
+                const int o = atomicAdd(&sp, nk);
+                plan_kids(nd, fl, R3, topo, [&](int q, int kid) {
+                    stack[o + q] = kid;
+                    owner[o + q] = (uint16_t)own;
+                });
+            }
+        }
+        next += f;
+    }
+    __syncthreads();
+    // the visits before every listed node: exclusive sums of the counts
+    int own = 0;
+    for (int k = 0; k < kPer; ++k) own += pos[tid * kPer + k];
+    int inc = own;
+#pragma unroll
+    for (int d = 1; d < kWave; d <<= 1) {
+        const int o = __shfl_up(inc, d, kWave);
+        inc += lane >= d ? o : 0;
+    }
+    if (lane == kWave - 1) wsum[wv] = inc;
+    __syncthreads();
+    int before = inc - own, total = 0;
+    for (int w = 0; w < kPlanBlock / kWave; ++w) {
+        before += w < wv ? wsum[w] : 0;
+        total += wsum[w];
+    }
+    for (int k = 0; k < kPer; ++k) {
+        const int w = pos[tid * kPer + k];
+        pos[tid * kPer + k] = before;
+        before += w;
+    }
+    __syncthreads();
+    const int step = plan_step(total);
+    int32_t *out = plan + (int64_t)g * kPlanStride;
+    for (int i = tid; i < n; i += kPlanBlock) {
+        const int v0 = pos[i], v1 = i + 1 < n ? pos[i + 1] : total;
+        for (int q = max((v0 + step - 1) / step, 1); q * step < v1; ++q) {
+            const bool up = i + 1 < n && q * step - v0 > v1 - q * step;  // nearer to the next
+            out[q] = vis[up ? i + 1 : i];
+        }
+    }
+    if (tid == 0) {
+        out[0] = total;
+        atomicAdd(sum, (unsigned long long)total);
+    }
 }
 
 // The cuts of every group's walk into parts of at most about `split` visits
 // (the first nodes of the parts after the first: nodes the plan reaches near
 // equal numbers of visits, in walk order), and the number of its parts (0: a
-// whole walk).  With step > 1, only every step-th node of the plan is a cut.
+// whole walk).  With step > 1, cuts are at multiples of step * kPlanStep visits
+// only.
 // One wavefront per group, a possible cut per lane: the plan is sorted, so a
 // cut counts where its node is past the one before it.  (One thread per group
 // was a chain of loads: 15 us at 50k points, now less than 10.)
@@ -993,12 +1154,14 @@ __global__ __launch_bounds__(256) void k_cuts(const int4 *__restrict__ groups,
         const int32_t *pl = plan + (int64_t)g * kPlanStride;
         int32_t *out = cuts + (int64_t)g * kPlanStride;
         const int V = pl[0];
-        const int visits = kPlanStep * step;  // between two nodes that can be cuts
-        const int kmax = min((V - 1) / visits, kPlanStride / step - 1);
+        const int ps = plan_step(V);
+        const int per = max(kPlanStep * step / ps, 1);  // nodes of the plan from one possible cut
+        const int visits = ps * per;                    // to the next, and the visits
+        const int kmax = min((V - 1) / visits, kPlanStride / per - 1);
         const int P = min((V + split - 1) / split, kmax + 1);
         const auto node_at = [&](int q) {
             const int v = (int)((int64_t)V * q / P);
-            return pl[step * min(max((v + visits / 2) / visits, 1), kmax)];
+            return pl[per * min(max((v + visits / 2) / visits, 1), kmax)];
         };
         for (int q0 = 1; q0 < P; q0 += kWave) {
             const int q = q0 + lane;
@@ -1148,14 +1311,24 @@ hipError_t make_tasks(wnnc_ctx_s *ctx, int tpl, int split) {
     const bool use_plan = split > 0 && tpl == 1;
     if (needs_plan(ctx, tpl, split)) {
         TRY(ctx->plan.ensure(g * kPlanStride));
-        TRY(ctx->plan_sum.ensure(1));
-        TRY(launch_zero_u64(ctx->plan_sum.p, 1, st));
+        TRY(ctx->plan_sum.ensure(2));
+        TRY(ctx->plan_longs.ensure(g));
+        TRY(launch_zero_u64(ctx->plan_sum.p, 2, st));
         hipLaunchKernelGGL(k_plan, dim3((unsigned)ng), dim3(kPlanBlock), 0, st, ctx->groups.p,
                            ctx->pts.p, ctx->cells.p, ctx->mom.p, ctx->topo.p, ctx->c, ctx->plan.p,
-                           ctx->plan_sum.p);
-        TRY(hipMemcpyAsync(&ctx->plan_visits, ctx->plan_sum.p, sizeof(unsigned long long),
-                           hipMemcpyDeviceToHost, st));
+                           ctx->plan_sum.p, ctx->plan_longs.p);
+        unsigned long long sum[2];
+        TRY(hipMemcpyAsync(sum, ctx->plan_sum.p, sizeof(sum), hipMemcpyDeviceToHost, st));
         TRY(hipStreamSynchronize(st));
+        if (sum[1] > 0) {
+            hipLaunchKernelGGL(k_plan_long, dim3((unsigned)sum[1]), dim3(kPlanBlock), 0, st,
+                               ctx->groups.p, ctx->pts.p, ctx->cells.p, ctx->mom.p, ctx->topo.p,
+                               ctx->c, ctx->plan.p, ctx->plan_sum.p, ctx->plan_longs.p);
+            TRY(hipGetLastError());
+            TRY(hipMemcpyAsync(sum, ctx->plan_sum.p, sizeof(sum), hipMemcpyDeviceToHost, st));
+            TRY(hipStreamSynchronize(st));
+        }
+        ctx->plan_visits = sum[0];
         ctx->plan_ok = true;
     }
     int eff = 0, step = 1;

@@ -1,0 +1,85 @@
+"""The parts of split walks against the walks themselves.
+
+The nodes that a 64-target group's walk visits are counted here in numpy from
+the exported tree and the representatives of a constant attribute (the
+attribute that walks are planned with), in FP32 as on the device.  From the
+visits V of every group follows the number of tasks: parts of
+
+    visits per part = the split size, or less on clouds whose walks are fewer
+                      than 16,384 parts of that size
+
+that is ceil(V / that) parts per group, cut at the plan's nodes.  A distance on
+the threshold may fall either way, so the counts may differ by 1 %.
+
+Walks of more than 4,096 visits (a large c) are planned by a kernel of their
+own.
+"""
+import numpy as np
+import pytest
+
+import synth
+
+pytestmark = pytest.mark.gpu
+FILL = 16384
+
+
+def walk_visits(ctx, x, c, group=64):
+    """Visits of every group's walk (one cloud)."""
+    import torch
+    if c >= 1e5:  # every node
+        return np.full(-(-len(x) // group), ctx.stats()["n_nodes"])
+    depth, leaf, begin, end, perm = ctx.tree()
+    xB = ctx.moments(torch.full((len(x),), 0.5, device=x.device))[0]
+    m = len(depth)
+    parent = np.full(m, -1)
+    last = {}
+    for k, d in enumerate(depth.tolist()):
+        last[d] = k
+        if d > 0:
+            parent[k] = last[d - 1]
+    order = np.argsort(parent[1:], kind="stable") + 1  # children by parent
+    first = np.searchsorted(parent[order], np.arange(m + 1))
+    thr2 = (np.float32(c) * np.ldexp(np.float32(1), 1 - depth).astype(np.float32)) ** 2
+    inner = leaf == 0
+    X = x.cpu().numpy()[perm]
+    V = []
+    for a in range(0, len(X), group):
+        t = X[a:a + group]
+        nodes, total = np.array([0]), 1
+        while len(nodes):
+            nodes = nodes[inner[nodes]]
+            d2 = np.full(len(nodes), np.inf, np.float32)
+            for p in t:
+                d2 = np.minimum(d2, ((p - xB[nodes]) ** 2).sum(1))
+            nodes = nodes[d2 <= thr2[nodes]]
+            nodes = np.concatenate([order[first[k]:first[k + 1]] for k in nodes]) if len(nodes) else nodes
+            total += len(nodes)
+        V.append(total)
+    return np.array(V)
+
+
+def expected_tasks(V, split):
+    """ceil(V / visits per part) per group."""
+    per = min(split, max(int(V.sum()) // FILL, 16))
+    return int(np.ceil(V / per).sum())
+
+
+@pytest.mark.parametrize("n,c", [(4000, 6.0), (20000, 8.0), (9000, 1e6), (20000, 1e6)])
+def test_long_walks_are_cut_evenly(n, c):
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2405_16634_amd as w
+    w.load_library()
+    print(f"[case] plan visits {n} c={c}", flush=True)
+    dev = torch.device("cuda:0")
+    ctx = w.Context(0)
+    x, _ = ctx.normalize(torch.from_numpy(synth.torus_knot(n, 5, with_init=False).points).to(dev))
+    ctx.build(x, c)
+    V = walk_visits(ctx, x, c)
+    got = ctx.stats()["n_tasks"]
+    print(f"  visits {V.min()}..{V.max()}, tasks {got}, expected {expected_tasks(V, 256)}", flush=True)
+    if n > 4000:
+        assert V.max() > 4096
+    assert abs(got - expected_tasks(V, 256)) <= 0.01 * got
+    ctx.close()
