@@ -1269,14 +1269,29 @@ __global__ __launch_bounds__(256) void k_emit_tasks(
 // 50k and 84 us instead of 74 at 100k, twice as many 73 us at 50k with the
 // combining pass twice as long.
 constexpr unsigned long long kFillParts = 16384;
-// Parts of the split size itself are cut at every kCoarseStep-th node of the
-// plan (64 visits): finer cuts balance them no better than 2 % (332 instead of
-// 338 us at 500k points), and these keep the grouping, and so the bits, of the
-// sums of large clouds independent of the plan's resolution.  Their sums are
-// rounded to FP32, once per 64 visits or more.  Shorter parts keep FP64 sums:
-// they also split walks that would otherwise be whole, whose sums meet FP32
-// only in the output.
+// Clouds that parts of kCoarseStep * kPlanStep visits (64) would fill are cut
+// into parts of the split size at every kCoarseStep-th node of the plan: finer
+// cuts balance them no better than 2 % (332 instead of 338 us at 500k points),
+// and these keep the grouping, and so the bits, of the sums of large clouds
+// independent of the plan's resolution.  Their sums are rounded to FP32, once
+// per 64 visits or more.  All other parts keep FP64 sums: they also split walks
+// that would otherwise be whole, whose sums meet FP32 only in the output.
 constexpr int kCoarseStep = 4;
+
+// How the current plan's walks are cut for a split size: parts of at most
+// `visits` visits (0: not), at every step-th node of the plan.
+struct CutRule {
+    int visits, step;
+};
+
+static CutRule cut_rule(const wnnc_ctx_s *ctx, int tpl, int split) {
+    if (split <= 0 || tpl != 1) return {0, 1};
+    const unsigned long long fill = ctx->plan_visits / kFillParts;
+    if (fill >= (unsigned long long)std::max(split, kPlanStep * kCoarseStep))
+        return {split, kCoarseStep};
+    return {(int)std::min<unsigned long long>(split, std::max<unsigned long long>(fill, kPlanStep)),
+            1};
+}
 
 // Wavefront tasks for tile shape tpl: each cloud's sorted targets cut into
 // runs of 64 * tpl, in Morton order, cloud after cloud.
@@ -1308,7 +1323,6 @@ hipError_t make_tasks(wnnc_ctx_s *ctx, int tpl, int split) {
                        hipMemcpyHostToDevice, st));
     hipLaunchKernelGGL(k_groups, dim3(blocks_for(g, 256)), dim3(256), 0, st, ctx->task_lo.p,
                        ctx->d_offsets.p, ctx->d_roots.p, ctx->nclouds, ng, per, ctx->groups.p);
-    const bool use_plan = split > 0 && tpl == 1;
     if (needs_plan(ctx, tpl, split)) {
         TRY(ctx->plan.ensure(g * kPlanStride));
         TRY(ctx->plan_sum.ensure(2));
@@ -1331,17 +1345,11 @@ hipError_t make_tasks(wnnc_ctx_s *ctx, int tpl, int split) {
         ctx->plan_visits = sum[0];
         ctx->plan_ok = true;
     }
-    int eff = 0, step = 1;
-    if (use_plan) {
-        TRY(ctx->cuts.ensure(g * kPlanStride));
-        eff = (int)std::min<unsigned long long>(
-            (unsigned long long)split,
-            std::max<unsigned long long>(ctx->plan_visits / kFillParts, kPlanStep));
-        if (eff == split) step = kCoarseStep;
-    }
-    const bool wide = use_plan && step < kCoarseStep;
+    const CutRule cut = cut_rule(ctx, tpl, split);
+    const bool wide = cut.visits > 0 && cut.step == 1;
+    if (cut.visits > 0) TRY(ctx->cuts.ensure(g * kPlanStride));
     hipLaunchKernelGGL(k_cuts, dim3(blocks_for(g, 256 / kWave)), dim3(256), 0, st, ctx->groups.p,
-                       ctx->plan.p, ng, eff, step, ctx->cuts.p, ctx->ncuts.p);
+                       ctx->plan.p, ng, cut.visits, cut.step, ctx->cuts.p, ctx->ncuts.p);
     hipLaunchKernelGGL(k_part_scan, dim3(1), dim3(kPartScan), 0, st, ctx->ncuts.p, ng,
                        ctx->part_off.p, ctx->split_off.p);
     uint32_t np = 0, ns = 0;

@@ -83,3 +83,29 @@ def test_long_walks_are_cut_evenly(n, c):
         assert V.max() > 4096
     assert abs(got - expected_tasks(V, 256)) <= 0.01 * got
     ctx.close()
+
+
+@pytest.mark.parametrize("n,c", [(2000, 2.0), (30000, 2.0), (20000, 8.0)])
+def test_smaller_splits_never_make_longer_parts(n, c):
+    """Clouds that parts of 64 visits do not fill (2,000 and 30,000 points) and
+    do fill (c = 8)."""
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2405_16634_amd as w
+    w.load_library()
+    print(f"[case] splits {n} c={c}", flush=True)
+    ctx = w.Context(0)
+    x, _ = ctx.normalize(torch.from_numpy(synth.fibonacci_sphere(n, 1).points).to("cuda:0"))
+    ctx.build(x, c)
+    tasks = []
+    for split in (0, 4096, 256, 128, 64, 63, 48, 33, 32, 17, 16, 1):
+        ctx.set_split(split)
+        st = ctx.stats()
+        tasks.append(st["n_tasks"])
+        if split == 0:
+            assert st["n_tasks"] == st["n_groups"]
+    print(f"  tasks {tasks}", flush=True)
+    assert all(a <= b for a, b in zip(tasks, tasks[1:])), tasks
+    assert tasks[1] >= 4 * tasks[0]
+    ctx.close()
