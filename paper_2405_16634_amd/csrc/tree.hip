@@ -1268,7 +1268,15 @@ __global__ __launch_bounds__(256) void k_emit_tasks(
 // 117 -> 107 us at 200k, 338 us at 500k either way; half as many parts take 40 us at
 // 50k and 84 us instead of 74 at 100k, twice as many 73 us at 50k with the
 // combining pass twice as long.
+// Where kFillGroups whole walks nearly fill the slots by themselves (forests of
+// small clouds), cutting them all only adds work, and the split size stands if
+// it leaves most of them whole: G in forests of 8,192 x 64 / 4,096 x 128 /
+// 3,072 x 128 points with the shorter parts 91 / 112 / 93 us, so 66 / 88 / 78 us;
+// of 4,096 x 64 / 2,048 x 128 (4,096 groups) 62 / 74 and whole 60 / 78 us.  (Most
+// walks cut in two take more rounds of wavefronts than either: 1,536 x 256
+// points 119 us, with the shorter parts 109.)
 constexpr unsigned long long kFillParts = 16384;
+constexpr int64_t kFillGroups = 5120;
 // Clouds that parts of kCoarseStep * kPlanStep visits (64) would fill are cut
 // into parts of the split size at every kCoarseStep-th node of the plan: finer
 // cuts balance them no better than 2 % (332 instead of 338 us at 500k points),
@@ -1284,11 +1292,21 @@ struct CutRule {
     int visits, step;
 };
 
+// Groups of `per` consecutive targets of one cloud.
+static int64_t group_count(const wnnc_ctx_s *ctx, int per) {
+    int64_t g = 0;
+    for (int c = 0; c < ctx->nclouds; ++c)
+        g += (ctx->offsets[c + 1] - ctx->offsets[c] + per - 1) / per;
+    return g;
+}
+
 static CutRule cut_rule(const wnnc_ctx_s *ctx, int tpl, int split) {
     if (split <= 0 || tpl != 1) return {0, 1};
     const unsigned long long fill = ctx->plan_visits / kFillParts;
     if (fill >= (unsigned long long)std::max(split, kPlanStep * kCoarseStep))
         return {split, kCoarseStep};
+    const int64_t ng = group_count(ctx, kWave);
+    if (ng >= kFillGroups && ctx->plan_visits <= (unsigned long long)ng * split) return {split, 1};
     return {(int)std::min<unsigned long long>(split, std::max<unsigned long long>(fill, kPlanStep)),
             1};
 }

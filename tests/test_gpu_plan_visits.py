@@ -109,3 +109,28 @@ def test_smaller_splits_never_make_longer_parts(n, c):
     assert all(a <= b for a, b in zip(tasks, tasks[1:])), tasks
     assert tasks[1] >= 4 * tasks[0]
     ctx.close()
+
+
+def test_forests_that_fill_the_chip_keep_most_walks_whole():
+    """6,144 groups of walks that are on average shorter than the split size;
+    a third of as many groups are cut into shorter parts."""
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2405_16634_amd as w
+    w.load_library()
+    rng = np.random.default_rng(4)
+    for clouds, whole in ((3072, True), (1024, False)):
+        print(f"[case] forest of {clouds}", flush=True)
+        p = torch.from_numpy(synth.random_unit(rng, 128 * clouds).astype(np.float32)).to("cuda:0")
+        off = [128 * k for k in range(clouds + 1)]
+        ctx = w.Context(0)
+        x, _ = ctx.normalize_batched(p, off)
+        ctx.build_batched(x, off)
+        st = ctx.stats()
+        ctx.close()
+        assert st["n_groups"] == 2 * clouds
+        if whole:
+            assert st["n_tasks"] <= 1.05 * st["n_groups"], st
+        else:
+            assert st["n_tasks"] >= 3 * st["n_groups"], st
