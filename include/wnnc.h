@@ -251,8 +251,10 @@ wnnc_status wnnc_set_prefetch(wnnc_ctx ctx, int on);
  * within 3 % of the fastest again in turn (three rounds), and keeps the
  * fastest (a setting later in the list must be faster by more than 1 %):
  * (tpl, split) = (1, 0), (2, 0), (4, 0), (1, 1024), (1, 512), (1, 256),
- * (1, 128), (1, 64), each with prefetch off and on (in that order); the
- * short splits fill the chip on small clouds (few target groups).  times_out (host,
+ * (1, 128), (1, 64), each with prefetch off and on (in that order).
+ * Splits that give the same parts on this tree (all that are longer than the
+ * parts a small cloud is cut into, see wnnc_set_split) are timed once and
+ * share that time.  times_out (host,
  * WNNC_AUTOTUNE_CONFIGS entries, may be NULL) receives the settings and
  * their times per iteration (the fastest run of each).  Then, on the chosen tiles, each operator
  * kind takes the other prefetch setting if its traversal launches are

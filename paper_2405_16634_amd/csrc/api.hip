@@ -638,11 +638,21 @@ wnnc_status wnnc_autotune(wnnc_ctx ctx, float w, wnnc_tile_time *times_out) {
         return WNNC_OK;
     };
     double tk[WNNC_AUTOTUNE_CONFIGS];
+    // the first pair with the same tasks (small clouds: most splits) is timed
+    // for all of them
+    int like[WNNC_AUTOTUNE_CONFIGS / 2];
     for (int k = 0; k < WNNC_AUTOTUNE_CONFIGS / 2; ++k) {
-        RETURN_IF(replace_tasks(ctx, cand[k][0], cand[k][1]));
+        like[k] = k;
+        for (int j = 0; j < k && like[k] == k; ++j)
+            if (cand[j][0] == cand[k][0] && same_tasks(ctx, cand[k][0], cand[j][1], cand[k][1]))
+                like[k] = j;
+        if (like[k] == k) RETURN_IF(replace_tasks(ctx, cand[k][0], cand[k][1]));
         for (int pf = 0; pf < 2; ++pf) {
-            double t;
-            RETURN_IF(time_setting(pf, kTuneReps, &t));
+            double t = 0.0;
+            if (like[k] == k)
+                RETURN_IF(time_setting(pf, kTuneReps, &t));
+            else
+                t = tk[2 * like[k] + pf];
             tk[2 * k + pf] = t;
             if (times_out) {
                 wnnc_tile_time &o = times_out[2 * k + pf];
@@ -664,7 +674,7 @@ wnnc_status wnnc_autotune(wnnc_ctx ctx, float w, wnnc_tile_time *times_out) {
         for (int c = 0; c < WNNC_AUTOTUNE_CONFIGS; ++c) t0 = std::min(t0, tk[c]);
         std::vector<int> near;
         for (int c = 0; c < WNNC_AUTOTUNE_CONFIGS; ++c)
-            if (tk[c] <= 1.03 * t0) near.push_back(c);
+            if (tk[c] <= 1.03 * t0 && like[c / 2] == c / 2) near.push_back(c);
         if (near.size() > 1) {
             for (int round = 0; round < kRetimeRounds; ++round) {
                 for (int c : near) {
@@ -675,6 +685,7 @@ wnnc_status wnnc_autotune(wnnc_ctx ctx, float w, wnnc_tile_time *times_out) {
                 }
             }
         }
+        for (int c = 0; c < WNNC_AUTOTUNE_CONFIGS; ++c) tk[c] = tk[2 * like[c / 2] + c % 2];
         if (times_out)
             for (int c = 0; c < WNNC_AUTOTUNE_CONFIGS; ++c) times_out[c].ms = tk[c];
         for (int c = 0; c < WNNC_AUTOTUNE_CONFIGS; ++c) {

@@ -66,6 +66,9 @@ hipError_t sort_queries(wnnc_ctx_s *ctx, const float *Q, int64_t M);
 // representatives of a constant attribute.
 bool needs_plan(const wnnc_ctx_s *ctx, int tpl, int split);
 hipError_t make_tasks(wnnc_ctx_s *ctx, int tpl, int split);
+// Whether two split sizes cut the walks alike (on the tree's plan, if there is
+// one: clouds too small to fill the chip have shorter parts than either).
+bool same_tasks(const wnnc_ctx_s *ctx, int tpl, int split_a, int split_b);
 
 // Moment pass (moments.hip): two launches, chunk pass then straddler pass.
 hipError_t launch_moments(wnnc_ctx_s *ctx, MomMode mode, const MomArgs &a);

@@ -1317,6 +1317,11 @@ bool needs_plan(const wnnc_ctx_s *ctx, int tpl, int split) {
     return split > 0 && tpl == 1 && !ctx->plan_ok;
 }
 
+bool same_tasks(const wnnc_ctx_s *ctx, int tpl, int split_a, int split_b) {
+    const CutRule a = cut_rule(ctx, tpl, split_a), b = cut_rule(ctx, tpl, split_b);
+    return a.visits == b.visits && a.step == b.step;
+}
+
 hipError_t make_tasks(wnnc_ctx_s *ctx, int tpl, int split) {
     hipStream_t st = ctx->stream;
     // (no tasks until all of them are there)
