@@ -327,6 +327,7 @@ wnnc_status wnnc_destroy(wnnc_ctx ctx) {
     ctx->ncuts.release();
     ctx->part_off.release();
     ctx->split_off.release();
+    ctx->part_count.release();
     ctx->split_groups.release();
     ctx->split_slot.release();
     ctx->finite_flag.release();
@@ -437,10 +438,12 @@ static hipError_t setup_tasks(wnnc_ctx_s *ctx, int tpl, int split) {
     return make_tasks(ctx, tpl, split);
 }
 
-// New tasks for the tree at hand.  If that fails, the old ones are partly
-// replaced: the tree counts as not built.
+// New tasks for the tree at hand, complete on return (the next walk may be on
+// another stream).  If that fails, the old ones are partly replaced: the tree
+// counts as not built.
 static wnnc_status replace_tasks(wnnc_ctx_s *ctx, int tpl, int split) {
-    const hipError_t e = setup_tasks(ctx, tpl, split);
+    hipError_t e = setup_tasks(ctx, tpl, split);
+    if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
     if (e == hipSuccess) return WNNC_OK;
     ctx->built = false;
     return fail(WNNC_EDEVICE, "tasks: %s (build the tree again)", hipGetErrorString(e));

@@ -105,6 +105,7 @@ struct wnnc_ctx_s {
     DevBuf<int32_t> task_slot;
     DevBuf<int32_t> task_chain;    // ntasks * kChainStride: ancestors of each task's first node
     DevBuf<int32_t> task_lo;       // nclouds + 1: group range of each cloud
+    std::vector<int32_t> task_lo_host;
     DevBuf<int4> split_groups;     // nsplit: first, last target; first, end part slot
     DevBuf<int32_t> split_slot;    // nsplit: group slot
     DevBuf<int2> gtab;             // ngroups: part range of each group (when gtab_ok)
@@ -119,7 +120,8 @@ struct wnnc_ctx_s {
     DevBuf<int32_t> plan_longs;    // those groups
     DevBuf<int32_t> cuts;          // ngroups * kPlanStride: first nodes of the parts after the first
     DevBuf<uint32_t> ncuts;        // ngroups: parts of a split walk (0: whole)
-    DevBuf<uint32_t> part_off, split_off;  // ngroups + 1: parts and split groups before each group
+    DevBuf<uint32_t> part_off, split_off;  // ngroups: parts and split groups before each group
+    DevBuf<uint32_t> part_count;   // parts, split groups
 
     // off-surface queries (wnnc_winding_at): sorted copies and their tasks
     DevBuf<unsigned long long> qkeys_a, qkeys_b;

@@ -1149,43 +1149,42 @@ __global__ __launch_bounds__(256) void k_cuts(const int4 *__restrict__ groups,
     const int g = blockIdx.x * (256 / kWave) + threadIdx.x / kWave;
     if (g >= ngroups) return;
     uint32_t cnt = 0;
-    if (split > 0) {
-        const int4 G = groups[g];
-        const int32_t *pl = plan + (int64_t)g * kPlanStride;
-        int32_t *out = cuts + (int64_t)g * kPlanStride;
-        const int V = pl[0];
-        const int ps = plan_step(V);
-        const int per = max(kPlanStep * step / ps, 1);  // nodes of the plan from one possible cut
-        const int visits = ps * per;                    // to the next, and the visits
-        const int kmax = min((V - 1) / visits, kPlanStride / per - 1);
-        const int P = min((V + split - 1) / split, kmax + 1);
-        const auto node_at = [&](int q) {
-            const int v = (int)((int64_t)V * q / P);
-            return pl[per * min(max((v + visits / 2) / visits, 1), kmax)];
-        };
-        for (int q0 = 1; q0 < P; q0 += kWave) {
-            const int q = q0 + lane;
-            int nd = G.w, prev = G.z;
-            if (q < P) {
-                nd = node_at(q);
-                if (q > 1) prev = max(prev, node_at(q - 1));
-            }
-            const bool cut = q < P && nd > prev && nd < G.w;
-            const uint64_t m = __ballot(cut);
-            if (cut) out[cnt + (uint32_t)__popcll(m & ((1ull << lane) - 1ull))] = nd;
-            cnt += (uint32_t)__popcll(m);
+    const int4 G = groups[g];
+    const int32_t *pl = plan + (int64_t)g * kPlanStride;
+    int32_t *out = cuts + (int64_t)g * kPlanStride;
+    const int V = pl[0];
+    const int ps = plan_step(V);
+    const int per = max(kPlanStep * step / ps, 1);  // nodes of the plan from one possible cut
+    const int visits = ps * per;                    // to the next, and the visits
+    const int kmax = min((V - 1) / visits, kPlanStride / per - 1);
+    const int P = min((V + split - 1) / split, kmax + 1);
+    const auto node_at = [&](int q) {
+        const int v = (int)((int64_t)V * q / P);
+        return pl[per * min(max((v + visits / 2) / visits, 1), kmax)];
+    };
+    for (int q0 = 1; q0 < P; q0 += kWave) {
+        const int q = q0 + lane;
+        int nd = G.w, prev = G.z;
+        if (q < P) {
+            nd = node_at(q);
+            if (q > 1) prev = max(prev, node_at(q - 1));
         }
+        const bool cut = q < P && nd > prev && nd < G.w;
+        const uint64_t m = __ballot(cut);
+        if (cut) out[cnt + (uint32_t)__popcll(m & ((1ull << lane) - 1ull))] = nd;
+        cnt += (uint32_t)__popcll(m);
     }
     if (lane == 0) nparts[g] = cnt > 0 ? cnt + 1 : 0u;
 }
 
-// Exclusive sums over the groups of their parts and of the split groups, by
-// one workgroup (both arrays have n + 1 entries).
+// Exclusive sums over the groups of their parts and of the split groups, and
+// the totals of both, by one workgroup.
 constexpr int kPartScan = 1024;
 
 __global__ __launch_bounds__(kPartScan) void k_part_scan(const uint32_t *__restrict__ nparts,
                                                          int n, uint32_t *__restrict__ part_off,
-                                                         uint32_t *__restrict__ split_off) {
+                                                         uint32_t *__restrict__ split_off,
+                                                         uint32_t *__restrict__ count) {
     constexpr int kItems = 8, kWaves = kPartScan / kWave;
     __shared__ uint32_t wp[kWaves], ws[kWaves];
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
@@ -1222,12 +1221,12 @@ __global__ __launch_bounds__(kPartScan) void k_part_scan(const uint32_t *__restr
         }
         __syncthreads();
     }
-    if (tid == 0) part_off[n] = cp, split_off[n] = cs;
+    if (tid == 0) count[0] = cp, count[1] = cs;
 }
 
 // The wavefront tasks of every group, in group order: group g's first task is
-// its parts before it plus the whole walks before it.  One wavefront per
-// group.
+// the parts before it plus the whole walks before it (no nparts: all walks are
+// whole).  One wavefront per group.
 __global__ __launch_bounds__(256) void k_emit_tasks(
     const int4 *__restrict__ groups, const int32_t *__restrict__ cuts,
     const uint32_t *__restrict__ nparts, const uint32_t *__restrict__ part_off,
@@ -1238,7 +1237,8 @@ __global__ __launch_bounds__(256) void k_emit_tasks(
     const int lane = threadIdx.x & (kWave - 1);
     if (g >= ngroups) return;
     const int4 G = groups[g];
-    const int P = (int)nparts[g], po = (int)part_off[g], so = (int)split_off[g];
+    const int P = nparts ? (int)nparts[g] : 0, po = nparts ? (int)part_off[g] : 0,
+              so = nparts ? (int)split_off[g] : 0;
     const int t0 = po + (g - so);
     if (gtab && lane == 0) gtab[g] = P > 0 ? make_int2(po, po + P) : make_int2(0, 0);
     if (P == 0) {
@@ -1328,7 +1328,9 @@ hipError_t make_tasks(wnnc_ctx_s *ctx, int tpl, int split) {
     ctx->gtab_ok = false;
     ctx->ntasks = ctx->nparts = ctx->nsplit = ctx->ngroups = 0;
     const int per = kWave * tpl;
-    std::vector<int32_t> lo(ctx->nclouds + 1);
+    // (kept: the copy may be under way when this returns)
+    std::vector<int32_t> &lo = ctx->task_lo_host;
+    lo.resize(ctx->nclouds + 1);
     int64_t g = 0;
     for (int c = 0; c < ctx->nclouds; ++c) {
         lo[c] = (int32_t)g;
@@ -1339,9 +1341,6 @@ hipError_t make_tasks(wnnc_ctx_s *ctx, int tpl, int split) {
     TRY(ctx->task_lo.ensure(ctx->nclouds + 1));
     TRY(ctx->groups.ensure(g));
     TRY(ctx->partial.ensure(3 * g));
-    TRY(ctx->ncuts.ensure(g));
-    TRY(ctx->part_off.ensure(g + 1));
-    TRY(ctx->split_off.ensure(g + 1));
     TRY(hipMemcpyAsync(ctx->task_lo.p, lo.data(), lo.size() * sizeof(int32_t),
                        hipMemcpyHostToDevice, st));
     hipLaunchKernelGGL(k_groups, dim3(blocks_for(g, 256)), dim3(256), 0, st, ctx->task_lo.p,
@@ -1370,16 +1369,22 @@ hipError_t make_tasks(wnnc_ctx_s *ctx, int tpl, int split) {
     }
     const CutRule cut = cut_rule(ctx, tpl, split);
     const bool wide = cut.visits > 0 && cut.step == 1;
-    if (cut.visits > 0) TRY(ctx->cuts.ensure(g * kPlanStride));
-    hipLaunchKernelGGL(k_cuts, dim3(blocks_for(g, 256 / kWave)), dim3(256), 0, st, ctx->groups.p,
-                       ctx->plan.p, ng, cut.visits, cut.step, ctx->cuts.p, ctx->ncuts.p);
-    hipLaunchKernelGGL(k_part_scan, dim3(1), dim3(kPartScan), 0, st, ctx->ncuts.p, ng,
-                       ctx->part_off.p, ctx->split_off.p);
-    uint32_t np = 0, ns = 0;
-    TRY(hipMemcpyAsync(&np, ctx->part_off.p + g, sizeof(np), hipMemcpyDeviceToHost, st));
-    TRY(hipMemcpyAsync(&ns, ctx->split_off.p + g, sizeof(ns), hipMemcpyDeviceToHost, st));
-    // (also: the host vector is released on return)
-    TRY(hipStreamSynchronize(st));
+    uint32_t count[2] = {0, 0};  // parts, split groups
+    if (cut.visits > 0) {
+        TRY(ctx->cuts.ensure(g * kPlanStride));
+        TRY(ctx->ncuts.ensure(g));
+        TRY(ctx->part_off.ensure(g));
+        TRY(ctx->split_off.ensure(g));
+        TRY(ctx->part_count.ensure(2));
+        hipLaunchKernelGGL(k_cuts, dim3(blocks_for(g, 256 / kWave)), dim3(256), 0, st,
+                           ctx->groups.p, ctx->plan.p, ng, cut.visits, cut.step, ctx->cuts.p,
+                           ctx->ncuts.p);
+        hipLaunchKernelGGL(k_part_scan, dim3(1), dim3(kPartScan), 0, st, ctx->ncuts.p, ng,
+                           ctx->part_off.p, ctx->split_off.p, ctx->part_count.p);
+        TRY(hipMemcpyAsync(count, ctx->part_count.p, sizeof(count), hipMemcpyDeviceToHost, st));
+        TRY(hipStreamSynchronize(st));
+    }
+    const uint32_t np = count[0], ns = count[1];
     const int64_t nt = (int64_t)np + (g - ns);
     // per group, its part range, when the groups are the 64-point blocks of
     // the sorted points (one group per wavefront, every cloud starting at a
@@ -1395,15 +1400,13 @@ hipError_t make_tasks(wnnc_ctx_s *ctx, int tpl, int split) {
     TRY(ctx->parts.ensure(std::max<int64_t>(wide ? nv : nv / 2, 1)));
     TRY(ctx->task_chain.ensure(nt * kChainStride));
     hipLaunchKernelGGL(k_emit_tasks, dim3(blocks_for(g * kWave, 256)), dim3(256), 0, st,
-                       ctx->groups.p, ctx->cuts.p, ctx->ncuts.p, ctx->part_off.p,
+                       ctx->groups.p, ctx->cuts.p, ns > 0 ? ctx->ncuts.p : nullptr, ctx->part_off.p,
                        ctx->split_off.p, ng, ctx->tasks.p, ctx->task_slot.p, ctx->split_groups.p,
                        ctx->split_slot.p, aligned ? ctx->gtab.p : nullptr);
     hipLaunchKernelGGL(k_task_chains, dim3(blocks_for(nt, 256)), dim3(256), 0, st, ctx->tasks.p,
                        ctx->cloud_of.p, ctx->d_roots.p, ctx->topo.p, ctx->mom.p, (int)nt,
                        ctx->task_chain.p);
     TRY(hipGetLastError());
-    // the tasks are complete on return: the next walk may be on another stream
-    TRY(hipStreamSynchronize(st));
     ctx->gtab_ok = aligned;
     ctx->parts_wide = wide;
     ctx->ntasks = (int)nt;

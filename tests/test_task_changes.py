@@ -98,3 +98,16 @@ else:
 print("failed", failed)
 """)
     assert int(out.split("failed")[1]) >= 8
+
+
+def test_whole_walks_need_no_cuts(run):
+    """Without split walks the tasks are the groups: no cuts are made, counted
+    or read back."""
+    run("""
+h = context(1)
+for change, v in ((lib.wnnc_set_split, 0), (lib.wnnc_set_tile, 4), (lib.wnnc_set_tile, 2)):
+    before = host.host_launches()
+    assert change(h, v) == 0, lib.wnnc_last_error()
+    assert host.host_launches() - before == 3, (v, host.host_launches() - before)
+lib.wnnc_destroy(h)
+""")
