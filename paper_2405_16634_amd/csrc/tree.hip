@@ -1260,23 +1260,25 @@ __global__ __launch_bounds__(256) void k_emit_tasks(
 }
 
 // Parts shorter than the split size where a cloud has too few of that size to
-// fill the chip: the walks are cut into about kFillParts parts (not below
-// kPlanStep visits each).  A part's chain of visits is what a small cloud's
-// walk takes; below two parts per wavefront slot, more of them only add the
-// visits of their ancestors.  A walk with parts of 256 visits -> of this rule:
-// 44.1 -> 9.7 us at 2k points, 52.6 -> 20.5 us at 20k, 53.1 -> 38 us at 50k,
-// 117 -> 107 us at 200k, 338 us at 500k either way; half as many parts take 40 us at
-// 50k and 84 us instead of 74 at 100k, twice as many 73 us at 50k with the
-// combining pass twice as long.
+// fill the chip (8,192 wavefront slots), not below kPlanStep visits each.  A
+// part's chain of visits is what a small cloud's walk takes; more of them add
+// the visits of their ancestors.  Up to kOneRoundVisits visits per part, one
+// round of wavefronts is best: just fewer parts than slots.  Longer parts leave
+// slots idle behind the longest, and kFillParts of them even that out; so they
+// do for leaves of several points (fewer nodes than points), whose visits
+// differ.  An iteration (us) with parts of 256 visits / about 16,384 parts /
+// one round: 254 / 174 / 154 at 20k points, 259 / 193 / 175 at 30k, 275 / 231 /
+// 229 at 50k, 303 / 273 / 289 at 70k, 354 / 343 / 352 at 100k, 429 / 172 / 189 at
+// 20k with leaves of up to 8; 2k points, 229 -> 100 with parts of 16 visits.
 // Where kFillGroups whole walks nearly fill the slots by themselves (forests of
 // small clouds), cutting them all only adds work, and the split size stands if
 // it leaves most of them whole: G in forests of 8,192 x 64 / 4,096 x 128 /
-// 3,072 x 128 points with the shorter parts 91 / 112 / 93 us, so 66 / 88 / 78 us;
-// of 4,096 x 64 / 2,048 x 128 (4,096 groups) 62 / 74 and whole 60 / 78 us.  (Most
-// walks cut in two take more rounds of wavefronts than either: 1,536 x 256
+// 3,072 x 128 points with the shorter parts 91 / 112 / 93 us, so 66 / 88 / 78 us.
+// (Most walks cut in two take more rounds of wavefronts than either: 1,536 x 256
 // points 119 us, with the shorter parts 109.)
 constexpr unsigned long long kFillParts = 16384;
 constexpr int64_t kFillGroups = 5120;
+constexpr unsigned long long kOneRoundVisits = 100;
 // Clouds that parts of kCoarseStep * kPlanStep visits (64) would fill are cut
 // into parts of the split size at every kCoarseStep-th node of the plan: finer
 // cuts balance them no better than 2 % (332 instead of 338 us at 500k points),
@@ -1307,8 +1309,14 @@ static CutRule cut_rule(const wnnc_ctx_s *ctx, int tpl, int split) {
         return {split, kCoarseStep};
     const int64_t ng = group_count(ctx, kWave);
     if (ng >= kFillGroups && ctx->plan_visits <= (unsigned long long)ng * split) return {split, 1};
-    return {(int)std::min<unsigned long long>(split, std::max<unsigned long long>(fill, kPlanStep)),
-            1};
+    unsigned long long visits = fill;
+    if (ng < kFillGroups && ctx->m > ctx->n) {
+        // (every group's last part is half full on average)
+        const unsigned long long one = ctx->plan_visits / (kFillParts / 2 - ng / 2) + 1;
+        if (one <= kOneRoundVisits) visits = one;
+    }
+    visits = std::max<unsigned long long>(visits, kPlanStep);
+    return {(int)std::min<unsigned long long>(split, visits), 1};
 }
 
 // Wavefront tasks for tile shape tpl: each cloud's sorted targets cut into
