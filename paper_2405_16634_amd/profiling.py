@@ -15,6 +15,8 @@ Three summaries, all from CSV output (``rocprofv3 ... -f csv -d DIR -o NAME``):
 * ``sq``: instruction counters (SQ_INSTS_VALU, ...) per dispatch of one
   kernel, and the fraction of the chip's wave64 vector-issue ceiling they
   take over the kernel's traced duration.
+* ``kernels``: duration, counters and HBM bytes of several kernels of one
+  command (its trace and PMC runs), for kernels outside the traversal.
 * ``moments``: the traffic of one moment-pass call (chunk pass plus
   straddler pass) on one workload, with their traced times and counters.
 
@@ -192,6 +194,41 @@ def sq(csv_paths, kernel: str, trace_csv: str, cmd: str, grid=None) -> dict:
     return d
 
 
+def kernels(csv_paths, trace_csv: str, cal_fetch_csv: str, cal_write_csv: str, mb: int, specs,
+            cmd: str) -> dict:
+    """specs: (label, regex, grid) triples.  Per dispatch of each: the traced
+    duration, the mean of every counter in csv_paths, the share of the chip's
+    vector-issue ceiling, and FETCH_SIZE and WRITE_SIZE as bytes (scaled by a
+    copy of known size, as in `traffic`)."""
+    cal = {}
+    for name, path in (("FETCH_SIZE", cal_fetch_csv), ("WRITE_SIZE", cal_write_csv)):
+        v = [float(r["Counter_Value"]) for r in _rows(path) if r["Counter_Name"] == name]
+        v = [x for x in v if x > 0.1 * mb * 1024.0]
+        cal[name] = mb * 1024.0 / (sum(v) / len(v))
+    rows = [r for p in csv_paths for r in _rows(p)]
+    trace = _rows(trace_csv)
+    out = []
+    for label, rx, grid in specs:
+        rx_ = re.compile(rx)
+        per = {}
+        for r in rows:
+            if _match(r, rx_, grid):
+                per.setdefault(r["Counter_Name"], []).append(float(r["Counter_Value"]))
+        c = {k: sum(v) / len(v) for k, v in per.items()}
+        t = [(int(r["End_Timestamp"]) - int(r["Start_Timestamp"])) * 1e-9
+             for r in trace if _match(r, rx_, grid)]
+        avg = sum(t) / len(t)
+        moved = {n: c.pop(n) * 1024.0 * cal[n] for n in cal if n in c}
+        out.append({"label": label, "kernel": rx, "grid_threads": grid, "dispatches": len(t),
+                    "trace_avg_us": round(avg * 1e6, 2),
+                    "read_bytes": round(moved.get("FETCH_SIZE", 0)),
+                    "write_bytes": round(moved.get("WRITE_SIZE", 0)),
+                    "gb_per_s": round(sum(moved.values()) / avg / 1e9, 1),
+                    "valu_issue_frac": round(c.get("SQ_INSTS_VALU", 0) / avg / VALU_ISSUE_PEAK, 4),
+                    "per_dispatch": {k: round(v, 2) for k, v in sorted(c.items())}})
+    return {"command": cmd, "kernels": out}
+
+
 def trace_markdown(stats_csv: str, title: str, cmd: str, groups=(), top: int = 25,
                    trace_csv=None, dispatch_groups=()) -> str:
     """groups: (label, regex) pairs; each gets the call-weighted average
@@ -266,6 +303,15 @@ def main():
     m.add_argument("--trace", default=None)
     m.add_argument("--cmd", required=True)
     m.add_argument("--out", required=True)
+    k = sub.add_parser("kernels")
+    k.add_argument("--csv", required=True, action="append")
+    k.add_argument("--trace", required=True)
+    k.add_argument("--cal-fetch", required=True)
+    k.add_argument("--cal-write", required=True)
+    k.add_argument("--mb", type=int, default=512)
+    k.add_argument("--kernel", required=True, action="append", metavar="LABEL=REGEX@GRID")
+    k.add_argument("--cmd", required=True)
+    k.add_argument("--out", required=True)
     a = ap.parse_args()
     if a.what == "trace":
         dg = []
@@ -278,6 +324,16 @@ def main():
                               trace_csv=a.trace, dispatch_groups=dg)
         with open(a.out, "w") as f:
             f.write(text)
+    elif a.what == "kernels":
+        specs = []
+        for g in a.kernel:
+            label, rest = g.split("=", 1)
+            rx, grid = rest.rsplit("@", 1)
+            specs.append((label, rx, int(grid)))
+        d = kernels(a.csv, a.trace, a.cal_fetch, a.cal_write, a.mb, specs, a.cmd)
+        with open(a.out, "w") as f:
+            json.dump(d, f, indent=1)
+            f.write("\n")
     elif a.what == "moments":
         d = moments(a.fetch, a.write, a.cal_fetch, a.cal_write, a.mb, a.chunk_grid, a.strad_grid,
                     a.cmd, a.sq, a.trace)
