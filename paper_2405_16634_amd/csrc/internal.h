@@ -78,11 +78,11 @@ hipError_t launch_moments(wnnc_ctx_s *ctx, MomMode mode, const MomArgs &a);
 hipError_t launch_moments_comb(wnnc_ctx_s *ctx, MomMode mode, const MomArgs &a,
                                const TravArgs &ta);
 // Whether a moment pass combines the walk before it: it can (gtab_ok), and it
-// does not take longer so.  Many FP64 parts per group (small clouds, whose
-// moment pass has a handful of workgroups) are added faster by a launch with a
-// wavefront per group: an iteration takes 104 instead of 108 us at 2k points,
-// 176 instead of 185 at 20k, 235 either way at 50k; with few parts per group
-// 343 instead of 339 us at 100k.
+// does not take longer so.  More than 16 FP64 parts per group (small clouds,
+// whose moment pass has a handful of workgroups) are added faster by a launch
+// with a wavefront per group: an iteration takes 104 instead of 108 us at 2k
+// points (36 parts), 176 instead of 185 at 20k (54 parts); with fewer parts 229
+// instead of 224 us at 50k (11 parts), 278 instead of 272 at 70k (16 parts).
 bool comb_in_moments(const wnnc_ctx_s *ctx);
 
 // Traversal (traverse.hip).

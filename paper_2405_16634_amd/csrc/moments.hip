@@ -487,7 +487,7 @@ static bool many_parts(const wnnc_ctx_s *ctx) {
 }
 
 bool comb_in_moments(const wnnc_ctx_s *ctx) {
-    return ctx->gtab_ok && !(ctx->parts_wide && many_parts(ctx));
+    return ctx->gtab_ok && !(ctx->parts_wide && ctx->nparts > 4 * kBatchFew * ctx->nsplit);
 }
 
 hipError_t launch_moments_comb(wnnc_ctx_s *ctx, MomMode mode, const MomArgs &args,

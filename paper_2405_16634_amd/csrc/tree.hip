@@ -1267,9 +1267,10 @@ __global__ __launch_bounds__(256) void k_emit_tasks(
 // slots idle behind the longest, and kFillParts of them even that out; so they
 // do for leaves of several points (fewer nodes than points), whose visits
 // differ.  An iteration (us) with parts of 256 visits / about 16,384 parts /
-// one round: 254 / 174 / 154 at 20k points, 259 / 193 / 175 at 30k, 275 / 231 /
-// 229 at 50k, 303 / 273 / 289 at 70k, 354 / 343 / 352 at 100k, 429 / 172 / 189 at
-// 20k with leaves of up to 8; 2k points, 229 -> 100 with parts of 16 visits.
+// one round: 254 / 174 / 154 at 20k points, 259 / 193 / 174 at 30k, 275 / 231 /
+// 222 at 50k (parts of 94 visits), a noisy 50k 259 / 238 (of 117), 70k 303 / 272 /
+// 289 (of 128), 100k 354 / 343 / 352, 20k with leaves of up to 8 429 / 172 / 189;
+// 2k points, 229 -> 100 with parts of 16 visits.
 // Where kFillGroups whole walks nearly fill the slots by themselves (forests of
 // small clouds), cutting them all only adds work, and the split size stands if
 // it leaves most of them whole: G in forests of 8,192 x 64 / 4,096 x 128 /
@@ -1278,7 +1279,7 @@ __global__ __launch_bounds__(256) void k_emit_tasks(
 // points 119 us, with the shorter parts 109.)
 constexpr unsigned long long kFillParts = 16384;
 constexpr int64_t kFillGroups = 5120;
-constexpr unsigned long long kOneRoundVisits = 100;
+constexpr unsigned long long kOneRoundVisits = 120;
 // Clouds that parts of kCoarseStep * kPlanStep visits (64) would fill are cut
 // into parts of the split size at every kCoarseStep-th node of the plan: finer
 // cuts balance them no better than 2 % (332 instead of 338 us at 500k points),

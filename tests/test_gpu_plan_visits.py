@@ -7,7 +7,7 @@ visits V of every group follows the number of tasks: parts of
 
     visits per part = the split size, or less on clouds whose walks are fewer
                       parts of that size than fill the chip: as many visits as
-                      make 8,192 parts, if that is 100 or less, else 16,384
+                      make 8,192 parts, if that is 120 or less, else 16,384
 
 that is ceil(V / that) parts per group, cut at the plan's nodes.  A distance on
 the threshold may fall either way, so the counts may differ by 1 %.
@@ -62,7 +62,7 @@ def walk_visits(ctx, x, c, group=64):
 def expected_tasks(V, split):
     """ceil(V / visits per part) per group."""
     fill, one = int(V.sum()) // FILL, int(V.sum()) // (FILL // 2 - len(V) // 2) + 1
-    per = min(split, max(one if one <= 100 else fill, 16))
+    per = min(split, max(one if one <= 120 else fill, 16))
     return int(np.ceil(V / per).sum())
 
 
