@@ -1268,9 +1268,10 @@ __global__ __launch_bounds__(256) void k_emit_tasks(
 // do for leaves of several points (fewer nodes than points), whose visits
 // differ.  An iteration (us) with parts of 256 visits / about 16,384 parts /
 // one round: 254 / 174 / 154 at 20k points, 259 / 193 / 174 at 30k, 275 / 231 /
-// 222 at 50k (parts of 94 visits), a noisy 50k 259 / 238 (of 117), 70k 303 / 272 /
-// 289 (of 128), 100k 354 / 343 / 352, 20k with leaves of up to 8 429 / 172 / 189;
-// 2k points, 229 -> 100 with parts of 16 visits.
+// 222 at 50k (parts of 94 visits), 303 / 272 / 289 at 70k (of 128), 354 / 343 /
+// 352 at 100k, 429 / 172 / 189 at 20k with leaves of up to 8 points; a noisy 50k
+// 259 with 16,384 parts, 238 with one round (of 117 visits); 2k points 229 with
+// parts of 256 visits, 100 with parts of 16.
 // Where kFillGroups whole walks nearly fill the slots by themselves (forests of
 // small clouds), cutting them all only adds work, and the split size stands if
 // it leaves most of them whole: G in forests of 8,192 x 64 / 4,096 x 128 /
