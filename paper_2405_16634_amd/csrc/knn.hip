@@ -18,7 +18,8 @@
 // vector instructions per wavefront and 836 us on a 164k-point sphere (VALU
 // 89 % busy), 945 us on a 100k-point knot; keys and FP64 minima took that to
 // 475 and 711 us, bound by the scalar unit and its loads, and nodes tested one
-// per lane to 269 and 265 us.
+// per lane to 270 and 275 us (8,800 and 9,700 vector instructions per
+// wavefront; VALU 86 and 58 % busy).
 // Requires points inside [-1,1]^3 (normalized clouds).
 #include <float.h>
 
