@@ -97,3 +97,28 @@ def test_long_planned_walks_cut_at_two_sizes(dev, oracle_mod):
         for split in (24, 1024):
             assert res[split][1] == res[0][1], split
             parity_bar.same_terms(f"split={split} {op}", res[split][0][q], res[0][0][q], mag)
+
+
+def test_long_planned_walks_of_a_wide_tree(dev):
+    """Exact sums of a tree of more than 2^16 nodes (child offsets beyond 16
+    bits): split walks count the pairs of whole walks, and every target's sum
+    of n terms agrees to 1e-6 of the largest."""
+    import torch
+    import paper_2405_16634_amd as w
+    n = 60000
+    print("[case] part paths wide", flush=True)
+    ctx = w.Context(0)
+    x, _ = ctx.normalize(torch.from_numpy(synth.fibonacci_sphere(n, 1).points).to(dev))
+    ctx.build(x, 1e6)
+    assert ctx.stats()["n_nodes"] > 1 << 16
+    mu = torch.from_numpy((synth.random_unit(np.random.default_rng(2), n) * 1e-3).astype(np.float32)).to(dev)
+    ctx.set_flags(w.FLAG_COUNT_PAIRS)
+    out, pairs = [], []
+    for split in (0, 256):
+        ctx.set_split(split)
+        ctx.reset_stats()
+        out.append(ctx.gradient(mu, 0.002).double())
+        pairs.append(ctx.stats()["pairs"][2])
+    ctx.close()
+    assert pairs[0] == pairs[1] == n * n
+    assert float((out[0] - out[1]).abs().max()) <= 1e-6 * float(out[0].abs().max())

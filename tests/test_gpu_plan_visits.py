@@ -60,13 +60,16 @@ def walk_visits(ctx, x, c, group=64):
 
 
 def expected_tasks(V, split):
-    """ceil(V / visits per part) per group."""
+    """ceil(V / visits per part) per group, cut at one of up to 256 nodes."""
     fill, one = int(V.sum()) // FILL, int(V.sum()) // (FILL // 2 - len(V) // 2) + 1
     per = min(split, max(one if one <= 120 else fill, 16))
-    return int(np.ceil(V / per).sum())
+    step = np.full(len(V), 16)
+    while (256 * step < V).any():
+        step[256 * step < V] *= 2
+    return int(np.minimum(np.ceil(V / per), (V - 1) // step + 1).sum())
 
 
-@pytest.mark.parametrize("n,c", [(4000, 6.0), (20000, 8.0), (9000, 1e6), (20000, 1e6)])
+@pytest.mark.parametrize("n,c", [(4000, 6.0), (20000, 8.0), (9000, 1e6), (20000, 1e6), (60000, 1e6)])
 def test_long_walks_are_cut_evenly(n, c):
     import torch
     if not torch.cuda.is_available():
